@@ -152,7 +152,8 @@ pp_status pp_attn_fwd(const pp_pack_desc* desc, pp_dtype dtype, int hq, int hkv,
  *
  * Workspace and mode: with ws_bytes >= pp_workspace_size's bwd the dQ pass
  * recomputes S and dP (scratch linear in the tokens, as Sec. 3.2.1's memory
- * argument assumes).  With ws_bytes >= pp_bwd_stored_ds_workspace_size's bwd
+ * argument assumes; a batch of few key tiles adds fp32 partial sums of dK and dV,
+ * at most a few hundred tiles of 128 keys, so that the whole chip works on it).  With ws_bytes >= pp_bwd_stored_ds_workspace_size's bwd
  * the key-major pass also stores dS (bf16, one value per query-key pair of
  * every 32 x 32 block with a visible pair, per query head) at the end of the
  * workspace and the dQ pass reads it back instead, so S, P and dP are computed

@@ -69,6 +69,8 @@ struct BwdParams {
   const QTileItem* dq_items;
   const KTileEntry* dq_ktiles;
   const KTileItem* kv_items;
+  const KTileSplit* kv_splits;
+  float* kv_part;  // fp32 partial dK, dV of the cut key tiles: [slot][kv-head][2][4 key blocks][32 * D]
   const int32_t* seg_lo;
   const int32_t* seg_hi;
   int hq, hkv, sumT;
@@ -218,7 +220,7 @@ __global__ __launch_bounds__(512, 1) void bwd_dkdv_kernel(BwdParams<TO> p) {
 
   const int nq = it.q_end - it.q_begin;
   const int nsteps = (nq + KBM - 1) / KBM;
-  const int n_iter = nq > 0 ? G * nsteps : 0;
+  const int n_iter = it.n_end;
   const int64_t q_stride = (int64_t)p.hq * D;
   const int64_t kv_stride = (int64_t)p.hkv * D;
 
@@ -240,6 +242,12 @@ __global__ __launch_bounds__(512, 1) void bwd_dkdv_kernel(BwdParams<TO> p) {
   Dma dma;
   dma.init(wave * (KBM / 8), q_stride, lane);
   int f_hh = 0, f_stp = 0;  // next step to fetch
+  if (it.n_begin > 0) {
+    f_hh = it.n_begin / nsteps;
+    f_stp = it.n_begin - f_hh * nsteps;
+  }
+  int c_hh = f_hh;  // head, within the kv-head's group, and first query of the step before the first
+  int qs = it.q_begin + (f_stp - 1) * KBM;
   auto issue = [&](int n) {
     DkdvStage<D>& sg = sm.st[n & 1];
     const int head = g * G + f_hh;
@@ -256,7 +264,7 @@ __global__ __launch_bounds__(512, 1) void bwd_dkdv_kernel(BwdParams<TO> p) {
       ++f_hh;
     }
   };
-  if (n_iter > 0) issue(0);
+  if (it.n_begin < n_iter) issue(it.n_begin);
 
   f32x16 acc_dk[D / 32], acc_dv[D / 32];
 #pragma unroll
@@ -273,9 +281,7 @@ __global__ __launch_bounds__(512, 1) void bwd_dkdv_kernel(BwdParams<TO> p) {
   }
   bool stored = false;  // this wave's last step ended with its two dS stores
 
-  int qs = it.q_begin - KBM;  // first query of the current step
-  int c_hh = 0;               // its head within the kv-head's group
-  for (int n = 0; n < n_iter; ++n) {
+  for (int n = it.n_begin; n < n_iter; ++n) {
     if (qs + KBM == it.q_begin + nsteps * KBM) {
       qs = it.q_begin;
       ++c_hh;
@@ -283,7 +289,7 @@ __global__ __launch_bounds__(512, 1) void bwd_dkdv_kernel(BwdParams<TO> p) {
       qs += KBM;
     }
     if constexpr (STORE_DS) {
-      // this wave's part of step n has landed (and, at n = 0, of K and V);
+      // this wave's part of step n has landed (and, at the first, of K and V);
       // the previous step's two dS stores, issued after it, may stay in
       // flight (vector-memory operations complete in order)
       if (stored) wait_vmem<2>();
@@ -291,7 +297,7 @@ __global__ __launch_bounds__(512, 1) void bwd_dkdv_kernel(BwdParams<TO> p) {
       stored = false;
       lds_barrier();  // ... for every wave; the stage of step n-1 is free
     } else {
-      wait_vmem<0>();  // this wave's part of step n (and, at n = 0, of K and V) has landed
+      wait_vmem<0>();  // this wave's part of step n (and, at the first, of K and V) has landed
       __syncthreads();  // ... for every wave; the stage of step n-1 is free
     }
     if (n + 1 < n_iter) issue(n + 1);
@@ -379,6 +385,34 @@ __global__ __launch_bounds__(512, 1) void bwd_dkdv_kernel(BwdParams<TO> p) {
   wait_vmem<0>();  // a tile of padding keys has no steps: its K/V DMA is still owed
   // add the second query half's partials into the first half's waves: first dK, then dV
   float* red = sm.red[kb];
+  if (it.slot >= 0) {
+    // a part of a cut tile: the sums go out as they lie in the accumulators
+#pragma unroll
+    for (int pass = 0; pass < 2; ++pass) {
+      const f32x16(&row)[D / 32] = pass == 0 ? acc_dk : acc_dv;
+      __syncthreads();  // stages (pass 0) or the previous pass's buffer are free
+      if (qb == 1) {
+#pragma unroll
+        for (int m = 0; m < D / 32; ++m)
+#pragma unroll
+          for (int r = 0; r < 16; ++r) red[(m * 16 + r) * 64 + lane] = row[m][r];
+      }
+      __syncthreads();
+      if (qb == 0) {
+        float* part = p.kv_part + ((((int64_t)it.slot * p.hkv + g) * 2 + pass) * 4 + kb) * (32 * D);
+#pragma unroll
+        for (int m = 0; m < D / 32; ++m)
+#pragma unroll
+          for (int r4 = 0; r4 < 4; ++r4) {
+            f32x4 v4;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) v4[e] = row[m][4 * r4 + e] + red[(m * 16 + 4 * r4 + e) * 64 + lane];
+            *reinterpret_cast<f32x4*>(part + ((m * 4 + r4) * 64 + lane) * 4) = v4;
+          }
+      }
+    }
+    return;
+  }
   TO* dkrow = p.dk + krow * D;
   TO* dvrow = p.dv + krow * D;
 #pragma unroll
@@ -409,6 +443,63 @@ __global__ __launch_bounds__(512, 1) void bwd_dkdv_kernel(BwdParams<TO> p) {
           store4<TO>(dst + 32 * m + 8 * r4 + 4 * hf,
                      f32x4{row[m][4 * r4], row[m][4 * r4 + 1], row[m][4 * r4 + 2], row[m][4 * r4 + 3]});
     }
+  }
+}
+
+// Adds the partial sums of the cut key tiles, in slot order, and finishes them
+// as the dK/dV pass does a whole tile's.  A stream over the partials (64 MB for
+// one 8B-shaped row): a wave takes the accumulator blocks hm and hm + D/64 of 32
+// keys (the two that hold a rotary pair) and one gradient, and has two parts'
+// 1 KB runs in flight.
+template <int D, typename TO, bool ROPE>
+__global__ __launch_bounds__(256) void bwd_kv_combine_kernel(BwdParams<TO> p) {
+  constexpr int HM = D / 64;
+  int b = blockIdx.x;
+  const int hm = b % HM;
+  b /= HM;
+  const int g = b % p.hkv;
+  b /= p.hkv;
+  const int pass = b & 1;
+  const KTileSplit sp = load_uniform(p.kv_splits + (b >> 1));
+  const int kb = threadIdx.x >> 6, lane = threadIdx.x & 63, hf = lane >> 5;
+  const int j = sp.k0 + kb * 32 + (lane & 31);
+  const int64_t stride = (int64_t)p.hkv * 2 * 4 * (32 * D);  // between slots
+  const float* part = p.kv_part + ((((int64_t)sp.slot0 * p.hkv + g) * 2 + pass) * 4 + kb) * (32 * D) + lane * 4;
+  f32x4 acc[2][4];
+#pragma unroll
+  for (int h = 0; h < 2; ++h)
+#pragma unroll
+    for (int r4 = 0; r4 < 4; ++r4) acc[h][r4] = f32x4{};
+#pragma unroll 2
+  for (int i = 0; i < sp.parts; ++i, part += stride)
+#pragma unroll
+    for (int h = 0; h < 2; ++h)
+#pragma unroll
+      for (int r4 = 0; r4 < 4; ++r4)
+        acc[h][r4] += *reinterpret_cast<const f32x4*>(part + ((hm + h * HM) * 4 + r4) * 256);
+  if (j >= sp.k_end) return;
+  const int64_t krow = (int64_t)(sp.tok0 + j) * p.hkv + g;
+  const float sc = pass == 0 ? p.scale : 1.f;
+  TO* dst = (pass == 0 ? p.dk : p.dv) + krow * D;
+#pragma unroll
+  for (int r4 = 0; r4 < 4; ++r4) {
+    f32x4 g1 = acc[0][r4] * sc, g2 = acc[1][r4] * sc;
+    const int c0 = 32 * hm + 8 * r4 + 4 * hf;
+    if constexpr (ROPE) {
+      if (pass == 0) {
+        const int pos = p.pos[sp.tok0 + j];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          float cs, sn;
+          rope_cos_sin(pos, p.inv_freq[c0 + e], cs, sn);
+          const float u = g1[e], w = g2[e];
+          g1[e] = u * cs + w * sn;
+          g2[e] = w * cs - u * sn;
+        }
+      }
+    }
+    store4<TO>(dst + c0, g1);
+    store4<TO>(dst + c0 + D / 2, g2);
   }
 }
 
@@ -777,6 +868,17 @@ __global__ __launch_bounds__(NW * 64, PP_DQ_MIN_WAVES) void bwd_dq_ds_kernel(Bwd
                  f32x4{acc[m][4 * r4], acc[m][4 * r4 + 1], acc[m][4 * r4 + 2], acc[m][4 * r4 + 3]});
 }
 
+// The sums of the cut key tiles, if there are any.
+template <int D, typename TO>
+hipError_t launch_kv_combine(const AttnBwdLaunch& a, const BwdParams<TO>& p, hipStream_t s) {
+  if (a.n_kv_splits == 0) return hipSuccess;
+  TimingScope t("pp_attn_bwd_kv_combine", s);
+  const dim3 grid((unsigned)(a.n_kv_splits * 2 * a.hkv * (D / 64)));
+  if (a.rope) hipLaunchKernelGGL((bwd_kv_combine_kernel<D, TO, true>), grid, dim3(256), 0, s, p);
+  else hipLaunchKernelGGL((bwd_kv_combine_kernel<D, TO, false>), grid, dim3(256), 0, s, p);
+  return hipGetLastError();
+}
+
 template <int D, typename TO>
 hipError_t launch_bwd_t(const AttnBwdLaunch& a, hipStream_t s) {
   BwdParams<TO> p;
@@ -795,6 +897,8 @@ hipError_t launch_bwd_t(const AttnBwdLaunch& a, hipStream_t s) {
   p.dq_items = a.dq_items;
   p.dq_ktiles = a.dq_ktiles;
   p.kv_items = a.kv_items;
+  p.kv_splits = a.kv_splits;
+  p.kv_part = a.kv_part;
   p.seg_lo = a.seg_lo;
   p.seg_hi = a.seg_hi;
   p.hq = a.hq;
@@ -828,6 +932,7 @@ hipError_t launch_bwd_t(const AttnBwdLaunch& a, hipStream_t s) {
       else hipLaunchKernelGGL((bwd_dkdv_kernel<D, TO, false, true>), grid, dim3(512), 0, s, p);
     }
     if ((e = hipGetLastError()) != hipSuccess) return e;
+    if ((e = launch_kv_combine<D, TO>(a, p, s)) != hipSuccess) return e;
     {
       TimingScope t("pp_attn_bwd_dq", s);
       const dim3 grid((unsigned)((int64_t)a.n_dq_items * a.hq));
@@ -850,8 +955,8 @@ hipError_t launch_bwd_t(const AttnBwdLaunch& a, hipStream_t s) {
     if (a.rope) hipLaunchKernelGGL((bwd_dkdv_kernel<D, TO, true, false>), grid, dim3(512), 0, s, p);
     else hipLaunchKernelGGL((bwd_dkdv_kernel<D, TO, false, false>), grid, dim3(512), 0, s, p);
   }
-  return hipGetLastError();
-
+  if ((e = hipGetLastError()) != hipSuccess) return e;
+  return launch_kv_combine<D, TO>(a, p, s);
 }
 
 }  // namespace

@@ -14,6 +14,7 @@
 #include <cstdarg>
 #include <cstdio>
 #include <cstring>
+#include <functional>
 #include <map>
 #include <mutex>
 #include <new>
@@ -250,7 +251,8 @@ int32_t key_tile_q_end(const Row& r, int32_t k0, int32_t k_end) {
   return end;
 }
 
-void build_kplan(const Batch& bt, int BN, std::vector<KTileItem>* out) {
+// Key tiles of the dK/dV pass, each one work item, longest first.
+void build_kplan(const Batch& bt, int BN, int G, std::vector<KTileItem>* out) {
   out->clear();
   for (int b = 0; b < bt.B; ++b) {
     const Row& r = bt.rows[b];
@@ -259,7 +261,6 @@ void build_kplan(const Batch& bt, int BN, std::vector<KTileItem>* out) {
       it.tok0 = r.tok0;
       it.k0 = k0;
       it.k_end = std::min(r.T, k0 + BN);
-      it.P = r.P;
       it.valid = r.valid;
       it.row = b;
       if (k0 >= r.valid) {
@@ -268,12 +269,94 @@ void build_kplan(const Batch& bt, int BN, std::vector<KTileItem>* out) {
         it.q_begin = k0;  // query k0 sees key k0
         it.q_end = key_tile_q_end(r, k0, it.k_end);
       }
+      it.n_begin = 0;
+      it.n_end = G * ((it.q_end - it.q_begin + kBwdBlockM - 1) / kBwdBlockM);
+      it.slot = -1;
       out->push_back(it);
     }
   }
   std::stable_sort(out->begin(), out->end(), [](const KTileItem& a, const KTileItem& b) {
-    return (a.q_end - a.q_begin) > (b.q_end - b.q_begin);
+    return a.n_end - a.n_begin > b.n_end - b.n_begin;
   });
+}
+
+// Parts of a tile of n (head, step) pairs when no part may exceed `most`.
+inline int split_parts(int n, int most) { return most > 0 && n > most ? (n + most - 1) / most : 1; }
+
+// Finish time, in steps, of one kv-head's items (longest first, each tile cut
+// so that no part exceeds `most` steps; 0: none) on `units` compute units that
+// each take the next item when they are free.
+double kplan_span(const std::vector<KTileItem>& tiles, int most, int units) {
+  // in steps of kBwdBlockM queries (2.0 us at head size 128, measured on 8B-shaped rows): 1.6 for a workgroup's K/V
+  // load and epilogue, 2 more for a part's fp32 sums and their addition
+  constexpr double kItem = 1.6, kPart = 2.0;
+  std::vector<std::pair<int, bool>> items;  // steps, part of a cut tile
+  for (const KTileItem& t : tiles) {
+    const int n = t.n_end - t.n_begin, parts = split_parts(n, most);
+    for (int i = 0; i < parts; ++i) items.emplace_back((int)((int64_t)n * (i + 1) / parts - (int64_t)n * i / parts), parts > 1);
+  }
+  std::stable_sort(items.begin(), items.end(), [](const auto& a, const auto& b) { return a.first > b.first; });
+  std::vector<double> busy(units, 0.0);  // min-heap of the units' finish times
+  double span = 0;
+  for (const auto& it : items) {
+    std::pop_heap(busy.begin(), busy.end(), std::greater<double>());
+    busy.back() += it.first + kItem + (it.second ? kPart : 0.0);
+    span = std::max(span, busy.back());
+    std::push_heap(busy.begin(), busy.end(), std::greater<double>());
+  }
+  return span;
+}
+
+// Cuts the longest key tiles of a batch that leaves compute units idle: with
+// few rows a prompt's first tile, which every later query of every head sees,
+// outlasts all others (one 8B-shaped row of 2080 tokens: 17 tiles x 8 kv-heads
+// on 256 units, the longest 132 steps against 37 a unit on average).  Batches of
+// more than 2 workgroups a unit are left alone: cutting their tiles costs more
+// in the parts' fixed work than it evens out (measured 0 to 14% slower).  On that
+// row the pass took 201 us whole and takes 97 us cut, plus 16 us for the sums.  A cut
+// has to shorten the estimated span by a tenth and by the 3 steps of the extra
+// launch that adds the partial sums.
+void split_kplan(int hkv, std::vector<KTileItem>* kv, std::vector<KTileSplit>* splits, int* slots) {
+  splits->clear();
+  *slots = 0;
+  if (kv->empty() || (int64_t)kv->size() * hkv > 2 * kComputeUnits) return;
+  const int units = std::max(1, kComputeUnits / hkv);
+  int64_t work = 0;
+  for (const KTileItem& t : *kv) work += t.n_end - t.n_begin;
+  const int even = (int)((work + units - 1) / units);
+  if ((*kv)[0].n_end < 8 || (*kv)[0].n_end <= even) return;  // the units' even share is the longer
+  const double whole = kplan_span(*kv, 0, units);
+  double best = whole;
+  int most = 0;
+  for (int div = 1; div <= 3; ++div) {
+    const int m = std::max(4, (even + div - 1) / div);
+    const double s = kplan_span(*kv, m, units) + 3.0;
+    if (s < best) {
+      best = s;
+      most = m;
+    }
+  }
+  if (most == 0 || best > 0.9 * whole) return;
+  std::vector<KTileItem> out;
+  for (const KTileItem& t : *kv) {
+    const int n = t.n_end - t.n_begin, parts = split_parts(n, most);
+    if (parts == 1) {
+      out.push_back(t);
+      continue;
+    }
+    splits->push_back(KTileSplit{t.tok0, t.k0, t.k_end, *slots, parts, 0});
+    for (int i = 0; i < parts; ++i) {
+      KTileItem p = t;
+      p.n_begin = (int32_t)((int64_t)n * i / parts);
+      p.n_end = (int32_t)((int64_t)n * (i + 1) / parts);
+      p.slot = (*slots)++;
+      out.push_back(p);
+    }
+  }
+  std::stable_sort(out.begin(), out.end(), [](const KTileItem& a, const KTileItem& b) {
+    return a.n_end - a.n_begin > b.n_end - b.n_begin;
+  });
+  kv->swap(out);
 }
 
 // The per-token arrays below are filled segment by segment: a validated row is
@@ -614,12 +697,15 @@ void plan_fwd(const Batch& bt, pp_dtype dtype, int hq, int hkv, int d, FwdPlan* 
 struct BwdPlan {
   QPlan dq;
   std::vector<KTileItem> kv;
+  std::vector<KTileSplit> kv_splits;
+  int kv_slots = 0;  // partial-sum slots of the cut key tiles
   std::vector<int32_t> seg_lo, seg_hi;
   std::vector<int32_t> row_kb0;
   std::vector<DsPanel> panels;
   int64_t ds_tiles = 0;  // per head; -1: the stored mode is not offered
   Layout lay;
-  size_t r_seg, r_seg_hi, r_dq_items, r_dq_kt, r_kv_items, r_row_kb0, r_panels, r_pos, r_freq, r_delta, r_nlse2;
+  size_t r_seg, r_seg_hi, r_dq_items, r_dq_kt, r_kv_items, r_kv_splits, r_row_kb0, r_panels, r_pos, r_freq, r_delta,
+      r_nlse2, r_kv_part;
   size_t r_ds = 0;
   size_t lean_total = 0;
   CastRegions cast;
@@ -627,7 +713,8 @@ struct BwdPlan {
 
 void plan_bwd(const Batch& bt, pp_dtype dtype, int hq, int hkv, int d, BwdPlan* p) {
   build_qplan(bt, kDqBlockM, kDqBlockN, &p->dq);
-  build_kplan(bt, kBwdBlockN, &p->kv);
+  build_kplan(bt, kBwdBlockN, hq / hkv, &p->kv);
+  split_kplan(hkv, &p->kv, &p->kv_splits, &p->kv_slots);
   build_seg_lo(bt, &p->seg_lo);
   build_seg_hi(bt, &p->seg_hi);
   p->lay = Layout();
@@ -636,6 +723,7 @@ void plan_bwd(const Batch& bt, pp_dtype dtype, int hq, int hkv, int d, BwdPlan* 
   p->r_dq_items = p->lay.add(p->dq.items.size() * sizeof(QTileItem));
   p->r_dq_kt = p->lay.add(p->dq.ktiles.size() * sizeof(KTileEntry));
   p->r_kv_items = p->lay.add(p->kv.size() * sizeof(KTileItem));
+  p->r_kv_splits = p->lay.add(p->kv_splits.size() * sizeof(KTileSplit));
   p->ds_tiles = build_ds_panels(bt, kBwdBlockN, &p->row_kb0, &p->panels);
   p->r_row_kb0 = p->lay.add(p->row_kb0.size() * 4);
   p->r_panels = p->lay.add(p->panels.size() * sizeof(DsPanel));
@@ -644,6 +732,7 @@ void plan_bwd(const Batch& bt, pp_dtype dtype, int hq, int hkv, int d, BwdPlan* 
   p->lay.meta_bytes = p->lay.total;
   p->r_delta = p->lay.add((size_t)hq * bt.sumT * 4);
   p->r_nlse2 = p->lay.add((size_t)hq * bt.sumT * 4);
+  p->r_kv_part = p->lay.add((size_t)p->kv_slots * hkv * 2 * kBwdBlockN * d * 4);
   if (dtype == PP_FP32) {
     p->cast.on = true;
     p->cast.q = p->lay.add((size_t)bt.sumT * hq * d * 2);
@@ -1099,6 +1188,7 @@ void bwd_image(const Batch& bt, const BwdPlan& p, int head_dim, const double* ro
   img.put(p.lay.regions[p.r_dq_items], p.dq.items.data(), p.dq.items.size() * sizeof(QTileItem));
   img.put(p.lay.regions[p.r_dq_kt], p.dq.ktiles.data(), p.dq.ktiles.size() * sizeof(KTileEntry));
   img.put(p.lay.regions[p.r_kv_items], p.kv.data(), p.kv.size() * sizeof(KTileItem));
+  img.put(p.lay.regions[p.r_kv_splits], p.kv_splits.data(), p.kv_splits.size() * sizeof(KTileSplit));
   img.put(p.lay.regions[p.r_row_kb0], p.row_kb0.data(), p.row_kb0.size() * 4);
   img.put(p.lay.regions[p.r_panels], p.panels.data(), p.panels.size() * sizeof(DsPanel));
   std::vector<int32_t> pos;
@@ -1153,6 +1243,9 @@ pp_status bwd_launch(const BwdPlan& p, void* ws, int sumT, pp_dtype dtype, int h
   a.n_dq_items = (int)p.dq.items.size();
   a.kv_items = (const KTileItem*)at(ws, p.lay, p.r_kv_items);
   a.n_kv_items = (int)p.kv.size();
+  a.kv_splits = (const KTileSplit*)at(ws, p.lay, p.r_kv_splits);
+  a.n_kv_splits = (int)p.kv_splits.size();
+  a.kv_part = (float*)at(ws, p.lay, p.r_kv_part);
   a.seg_lo = (const int32_t*)at(ws, p.lay, p.r_seg);
   a.seg_hi = (const int32_t*)at(ws, p.lay, p.r_seg_hi);
   a.hq = hq;

@@ -80,6 +80,12 @@ struct AttnBwdLaunch {
   int n_dq_items;
   const KTileItem* kv_items;
   int n_kv_items;
+  // key tiles whose (head, step) pairs are spread over several items, and the
+  // fp32 partial dK and dV of every (slot, kv-head): 2 * kBwdBlockN * head_dim
+  // floats each
+  const KTileSplit* kv_splits;
+  int n_kv_splits;
+  float* kv_part;
   const int32_t* seg_lo;
   const int32_t* seg_hi;  // per token: one past the last query that sees it as a key
   int hq, hkv, head_dim;

@@ -65,9 +65,8 @@ constexpr int kFwdBlockN = PP_FWD_BLOCK_N;  // keys per forward k-tile (32 or 64
 constexpr int kDqBlockM = 32 * kDqWaves;    // queries per dQ workgroup
 constexpr int kDqBlockN = PP_DQ_BLOCK_N;    // keys per dQ k-tile (32 or 64)
 constexpr int kBwdBlockN = 128;             // keys per dK/dV workgroup (8 waves: 4 key blocks x 2)
-
-
 constexpr int kBwdBlockM = 64;              // queries per dK/dV inner step
+constexpr int kComputeUnits = 256;          // of an MI355X
 
 // An entry of a query tile's key-tile list: the tile's first key (row-relative)
 // and, per 32-query block w of the query tile, a 2-bit class of the block's
@@ -100,16 +99,33 @@ struct QTileItem {
   int32_t row;     // row index (diagnostics)
 };
 
-// One key tile: keys [k0, k_end) of a row and the query range that sees them.
+// One work item of the dK/dV pass: keys [k0, k_end) of a row, the query range
+// that sees them, and the run [n_begin, n_end) of the tile's (head, step) pairs
+// that the item walks -- steps of kBwdBlockM queries, head by head.  A tile cut
+// into several items has one partial-sum slot per item; a whole tile (slot -1)
+// writes its gradients itself.
 struct KTileItem {
   int32_t tok0;
   int32_t k0;
   int32_t k_end;
-  int32_t P;
   int32_t valid;
   int32_t q_begin;  // first query that sees a key of the tile
   int32_t q_end;    // one past the last such query
   int32_t row;
+  int32_t n_begin;
+  int32_t n_end;
+  int32_t slot;
+};
+
+// A key tile cut into several items: its partial sums sit in `parts`
+// consecutive slots and are added in slot order.
+struct KTileSplit {
+  int32_t tok0;
+  int32_t k0;
+  int32_t k_end;
+  int32_t slot0;
+  int32_t parts;
+  int32_t pad;
 };
 
 // Where the backward keeps dS of one 32-key block (row-relative block KB of
