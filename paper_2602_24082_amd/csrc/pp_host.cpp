@@ -704,7 +704,7 @@ struct BwdPlan {
   std::vector<DsPanel> panels;
   int64_t ds_tiles = 0;  // per head; -1: the stored mode is not offered
   Layout lay;
-  size_t r_seg, r_seg_hi, r_dq_items, r_dq_kt, r_kv_items, r_kv_splits, r_row_kb0, r_panels, r_pos, r_freq, r_delta,
+  size_t r_seg, r_seg_hi, r_dq_items, r_dq_kt, r_kv_items, r_kv_splits, r_row_kb0, r_panels, r_pos, r_freq, r_ndelta,
       r_nlse2, r_kv_part;
   size_t r_ds = 0;
   size_t lean_total = 0;
@@ -730,7 +730,7 @@ void plan_bwd(const Batch& bt, pp_dtype dtype, int hq, int hkv, int d, BwdPlan* 
   p->r_pos = p->lay.add((size_t)bt.sumT * 4);
   p->r_freq = p->lay.add((size_t)d / 2 * 8);
   p->lay.meta_bytes = p->lay.total;
-  p->r_delta = p->lay.add((size_t)hq * bt.sumT * 4);
+  p->r_ndelta = p->lay.add((size_t)hq * bt.sumT * 4);
   p->r_nlse2 = p->lay.add((size_t)hq * bt.sumT * 4);
   p->r_kv_part = p->lay.add((size_t)p->kv_slots * hkv * 2 * kBwdBlockN * d * 4);
   if (dtype == PP_FP32) {
@@ -1236,7 +1236,7 @@ pp_status bwd_launch(const BwdPlan& p, void* ws, int sumT, pp_dtype dtype, int h
   a.dq = dq;
   a.dk = dk;
   a.dv = dv;
-  a.delta = (float*)at(ws, p.lay, p.r_delta);
+  a.ndelta = (float*)at(ws, p.lay, p.r_ndelta);
   a.nlse2 = (float*)at(ws, p.lay, p.r_nlse2);
   a.dq_items = (const QTileItem*)at(ws, p.lay, p.r_dq_items);
   a.dq_ktiles = (const KTileEntry*)at(ws, p.lay, p.r_dq_kt);

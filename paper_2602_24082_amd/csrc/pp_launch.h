@@ -73,7 +73,7 @@ struct AttnBwdLaunch {
   void* dq;
   void* dk;
   void* dv;
-  float* delta;              // [hq, sumT] scratch: dO . O per query
+  float* ndelta;             // [hq, sumT] scratch: -dO . O per query
   float* nlse2;              // [hq, sumT] scratch: -LSE * log2(e)
   const QTileItem* dq_items;
   const KTileEntry* dq_ktiles;
