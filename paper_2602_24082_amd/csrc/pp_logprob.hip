@@ -97,59 +97,75 @@ struct Vec16<float> {
   }
 };
 
+// A logit row of `vocab` elements starting at x as 16-byte vectors: `head`
+// elements up to the first 16-byte boundary, `nvec` vectors, and what is left.
+// Rows of a vocabulary that is no multiple of a vector's elements start anywhere;
+// each of the head and tail elements (fewer than two vectors together) belongs to
+// one thread (extra()).
+template <typename T>
+struct RowSplit {
+  static constexpr int N = 16 / (int)sizeof(T);
+  int head, nvec, n_extra;
+  __device__ __forceinline__ RowSplit(const T* x, int vocab) {
+    const int off = (int)(reinterpret_cast<uintptr_t>(x) & 15);
+    head = min(vocab, ((16 - off) & 15) / (int)sizeof(T));
+    nvec = (vocab - head) / N;
+    n_extra = vocab - nvec * N;
+  }
+  // index of the head or tail element of thread tid (valid for tid < n_extra)
+  __device__ __forceinline__ int extra(int tid) const { return tid < head ? tid : tid + nvec * N; }
+};
+
 // ln sum_v exp(x[v]) of one logit row, for every thread of a kLpThreads
-// workgroup: one streaming pass of 16-byte loads (kLpUnroll in flight per
-// thread) keeping an online (max, sum) per thread, then a fixed-order
-// workgroup combine.
+// workgroup: one streaming pass of aligned 16-byte loads (kLpUnroll in flight per
+// thread) keeping an online (max, sum) per thread, the row's head and tail
+// elements last, then a fixed-order workgroup combine.  HBM bound.  Rows that
+// start on no 16-byte boundary used to be read element by element: 2224 rows of
+// 50257 fp32 took 135 us and take 69 us (6.5 TB/s).
 template <typename T>
 __device__ float row_logsumexp(const T* __restrict__ x, int vocab) {
   const int tid = threadIdx.x;
   MaxSum acc = {kNegInf, 0.f};
   constexpr int N = Vec16<T>::N;
-  int64_t done = 0;  // elements handled by the vector path
-  if ((reinterpret_cast<uintptr_t>(x) & 15) == 0) {
-    const int nvec = vocab / N;
-    const u32x4* xv = reinterpret_cast<const u32x4*>(x);
-    for (int base = 0; base < nvec; base += kLpThreads * kLpUnroll) {
-      u32x4 u[kLpUnroll];
+  const RowSplit<T> rs(x, vocab);
+  const int nvec = rs.nvec;
+  const u32x4* xv = reinterpret_cast<const u32x4*>(x + rs.head);
+  const float xe = tid < rs.n_extra ? elem<T>(x, rs.extra(tid)) : kNegInf;
+  for (int base = 0; base < nvec; base += kLpThreads * kLpUnroll) {
+    u32x4 u[kLpUnroll];
 #pragma unroll
-      for (int j = 0; j < kLpUnroll; ++j) {
-        const int vi = base + j * kLpThreads + tid;
-        u[j] = vi < nvec ? __builtin_nontemporal_load(xv + vi) : u32x4{0, 0, 0, 0};
+    for (int j = 0; j < kLpUnroll; ++j) {
+      const int vi = base + j * kLpThreads + tid;
+      u[j] = vi < nvec ? __builtin_nontemporal_load(xv + vi) : u32x4{0, 0, 0, 0};
+    }
+    float f[kLpUnroll * N];
+#pragma unroll
+    for (int j = 0; j < kLpUnroll; ++j) Vec16<T>::unpack(u[j], f + j * N);
+    float mloc = kNegInf;
+#pragma unroll
+    for (int j = 0; j < kLpUnroll; ++j) {
+      const int vi = base + j * kLpThreads + tid;
+      if (vi < nvec) {
+#pragma unroll
+        for (int e = 0; e < N; ++e) mloc = fmaxf(mloc, f[j * N + e]);
       }
-      float f[kLpUnroll * N];
-#pragma unroll
-      for (int j = 0; j < kLpUnroll; ++j) Vec16<T>::unpack(u[j], f + j * N);
-      float mloc = kNegInf;
+    }
+    const float m = fmaxf(acc.m, mloc);
+    if (m != kNegInf) {
+      const float ml = m * kLog2e;
+      float s = acc.s * fast_exp2(acc.m * kLog2e - ml);
 #pragma unroll
       for (int j = 0; j < kLpUnroll; ++j) {
         const int vi = base + j * kLpThreads + tid;
         if (vi < nvec) {
 #pragma unroll
-          for (int e = 0; e < N; ++e) mloc = fmaxf(mloc, f[j * N + e]);
+          for (int e = 0; e < N; ++e) s += fast_exp2(fmaf(f[j * N + e], kLog2e, -ml));
         }
       }
-      const float m = fmaxf(acc.m, mloc);
-      if (m != kNegInf) {
-        const float ml = m * kLog2e;
-        float s = acc.s * fast_exp2(acc.m * kLog2e - ml);
-#pragma unroll
-        for (int j = 0; j < kLpUnroll; ++j) {
-          const int vi = base + j * kLpThreads + tid;
-          if (vi < nvec) {
-#pragma unroll
-            for (int e = 0; e < N; ++e) s += fast_exp2(fmaf(f[j * N + e], kLog2e, -ml));
-          }
-        }
-        acc = {m, s};
-      }
+      acc = {m, s};
     }
-    done = (int64_t)nvec * N;
   }
-  for (int64_t i = done + tid; i < vocab; i += kLpThreads) {
-    const float v = elem<T>(x, i);
-    acc = combine(acc, MaxSum{v, 1.f});
-  }
+  if (tid < rs.n_extra) acc = combine(acc, MaxSum{xe, 1.f});
   // workgroup reduction of (m, s)
   for (int off = 32; off > 0; off >>= 1) {
     MaxSum o;
@@ -207,6 +223,13 @@ struct Pack16<float> {
   }
 };
 
+// A 16-byte vector of T at any address that is a multiple of T's size (one
+// global load or store all the same: the GPU takes unaligned vectors).
+template <typename T>
+struct __attribute__((packed, aligned(sizeof(T)))) Vec16Any {
+  u32x4 v;
+};
+
 // Log-prob backward: one workgroup per flat logit row r.  With c = the sum of
 // g over the labels that row r predicts,
 //   dlogits[r, v] = -c softmax(x_r)[v] + sum_{labels y = v} g,
@@ -226,15 +249,13 @@ __global__ __launch_bounds__(kLpThreads) void logprob_bwd_kernel(LogprobBwdLaunc
   if (a.gathered && a.row_index && tid == 0) a.row_index[item] = (int32_t)r;
   T* out = reinterpret_cast<T*>(a.dlogits) + o_row * (int64_t)vocab;
   constexpr int N = Vec16<T>::N;
-  const bool aligned = ((o_row * (int64_t)vocab * (int64_t)sizeof(T)) & 15) == 0 &&
-                       ((r * (int64_t)vocab * (int64_t)sizeof(T)) & 15) == 0 &&
-                       (reinterpret_cast<uintptr_t>(a.dlogits) & 15) == 0 &&
-                       (reinterpret_cast<uintptr_t>(a.logits) & 15) == 0;
-  const int nvec = aligned ? vocab / N : 0;
+  // the output row's own 16-byte boundaries; the input row may lie on others
+  const RowSplit<T> rs(out, vocab);
+  const int nvec = rs.nvec;
+  u32x4* ov = reinterpret_cast<u32x4*>(out + rs.head);
   if (item < 0) {
-    u32x4* ov = reinterpret_cast<u32x4*>(out);
     for (int vi = tid; vi < nvec; vi += kLpThreads) __builtin_nontemporal_store(u32x4{0, 0, 0, 0}, ov + vi);
-    for (int64_t v = (int64_t)nvec * N + tid; v < vocab; v += kLpThreads) out[v] = (T)0.f;
+    if (tid < rs.n_extra) out[rs.extra(tid)] = (T)0.f;
     return;
   }
   const LogitRowItem it = a.rows[item];
@@ -273,14 +294,14 @@ __global__ __launch_bounds__(kLpThreads) void logprob_bwd_kernel(LogprobBwdLaunc
       }
     }
   };
-  const u32x4* xv = reinterpret_cast<const u32x4*>(x);
-  u32x4* ov = reinterpret_cast<u32x4*>(out);
+  const Vec16Any<T>* xv = reinterpret_cast<const Vec16Any<T>*>(x + rs.head);
+  const float xe = tid < rs.n_extra ? elem<T>(x, rs.extra(tid)) : 0.f;
   for (int base = 0; base < nvec; base += kLpThreads * kLpUnroll) {
     u32x4 u[kLpUnroll];
 #pragma unroll
     for (int j = 0; j < kLpUnroll; ++j) {
       const int vi = base + j * kLpThreads + tid;
-      u[j] = vi < nvec ? xv[vi] : u32x4{0, 0, 0, 0};
+      u[j] = vi < nvec ? xv[vi].v : u32x4{0, 0, 0, 0};
     }
 #pragma unroll
     for (int j = 0; j < kLpUnroll; ++j) {
@@ -290,7 +311,7 @@ __global__ __launch_bounds__(kLpThreads) void logprob_bwd_kernel(LogprobBwdLaunc
         Vec16<T>::unpack(u[j], f);
 #pragma unroll
         for (int e = 0; e < N; ++e) f[e] = -c * fast_exp2(fmaf(f[e], kLog2e, -lse2));
-        label_terms(f, vi * N, N);
+        label_terms(f, rs.head + vi * N, N);
         if (bad) {
 #pragma unroll
           for (int e = 0; e < N; ++e) f[e] = __builtin_nanf("");
@@ -299,72 +320,91 @@ __global__ __launch_bounds__(kLpThreads) void logprob_bwd_kernel(LogprobBwdLaunc
       }
     }
   }
-  for (int64_t v = (int64_t)nvec * N + tid; v < vocab; v += kLpThreads) {
+  if (tid < rs.n_extra) {
     float f[N] = {};
-    f[0] = -c * fast_exp2(fmaf(elem<T>(x, v), kLog2e, -lse2));
-    label_terms(f, (int)v, 1);
-    out[v] = (T)(bad ? __builtin_nanf("") : f[0]);
+    f[0] = -c * fast_exp2(fmaf(xe, kLog2e, -lse2));
+    label_terms(f, rs.extra(tid), 1);
+    out[rs.extra(tid)] = (T)(bad ? __builtin_nanf("") : f[0]);
   }
 }
 
-// Log-prob backward with the row held in registers: one 1024-thread workgroup
-// per flat logit row.  A needed row is read from HBM once -- thread t loads the
-// 16-byte vectors t, t + 1024, ... (up to kLpbVecs of them) -- its logsumexp is
-// formed from the registers (thread maximum, then thread sum of exponentials,
-// then a fixed-order workgroup combine), and the gradient is computed from the
-// same registers and streamed out, so each row costs one read and one write of
-// HBM (the two-pass kernel above reads it twice).  Rows that predict nothing
-// are streamed zeros.  Used when the row's 16-byte vectors fit
-// (vocab <= kLpbThreads * kLpbVecs * elements per vector: 155648 bf16 or 77824
-// fp32 values, so a 152064-entry bf16 vocabulary fits as well as a 128256-entry
-// one) and rows are 16-byte aligned.  1024 threads x 19 vectors take 128 VGPRs
-// without spilling, the most that still allows 4 waves per SIMD; that shape
-// kept HBM busier than 512 x 40 (2 waves per SIMD, 0.73 against 0.77 ms on the
-// 8B-shaped batch) and than 768 x 27 or 1024 x 20 (both spill).
-#ifndef PP_LPB_THREADS
-#define PP_LPB_THREADS 1024
-#endif
-#ifndef PP_LPB_VECS
-#define PP_LPB_VECS 19
-#endif
-constexpr int kLpbThreads = PP_LPB_THREADS;
-constexpr int kLpbVecs = PP_LPB_VECS;
-
+// Log-prob backward with the row held in registers: one workgroup per flat
+// logit row.  A needed row is read from HBM once -- thread t loads the 16-byte
+// vectors t, t + THREADS, ... (R of them at most) -- its logsumexp is formed from
+// the registers (thread maximum, then thread sum of exponentials, then a
+// fixed-order workgroup combine), and the gradient is computed from the same
+// registers and streamed out, so each row costs one read and one write of HBM
+// (the two-pass kernel above reads it twice).  Rows that predict nothing are
+// streamed zeros.
+//
+// A workgroup first loads, then computes, then stores, so several of them per
+// compute unit are what keeps loads and stores in flight together, as far as the
+// rows leave registers for them (launch_logprob_bwd picks the shape):
+//   512 threads x 8 vectors (4 workgroups): up to 32768 bf16 or 16384 fp32 values,
+//   1024 x 8 (2 workgroups): twice that,
+//   1024 x 19 (128 VGPRs, one workgroup): 155648 bf16 or 77824 fp32 values, so a
+//     152064-entry bf16 vocabulary fits as well as a 128256-entry one; it kept HBM
+//     busier than 512 x 40 (0.73 against 0.77 ms on the 8B-shaped batch) and than
+//     768 x 27 or 1024 x 20 (both spill).
+// 3864 gathered rows of 32000 bf16 values take 92 us (155 us with the 1024 x 19
+// shape), 2224 of 50257 bf16 86 us.
+//
+// EDGE: rows that start on no 16-byte boundary.  The vectors lie on the input
+// row's boundaries (so the logsumexp does not depend on where the output goes),
+// the stores where the output row has them, and one thread each takes the head
+// and tail elements; that costs registers (R 18 instead of 19).  The
+// two-pass kernel with element loads took 283 us on those 2224 rows, and 814 us
+// instead of 375 us on 2047 rows of 151999 bf16 values (now two passes of vectors).
 template <int R>
 __device__ __forceinline__ void opaque(u32x4 (&u)[R]) {
 #pragma unroll
   for (int j = 0; j < R; ++j) asm volatile("" : "+v"(u[j]));
 }
 
-template <typename T>
-__global__ __launch_bounds__(kLpbThreads) void logprob_bwd_reg_kernel(LogprobBwdLaunch a) {
+template <typename T, int THREADS, int R, bool EDGE>
+__global__ __launch_bounds__(THREADS, R <= 8 ? 8 : 4) void logprob_bwd_reg_kernel(LogprobBwdLaunch a) {
   constexpr int N = Vec16<T>::N;
-  constexpr int NW = kLpbThreads / 64;
+  constexpr int NW = THREADS / 64;
   const int tid = threadIdx.x;
   const int vocab = a.vocab;
-  const int nvec = vocab / N;  // vocab % N == 0 here
   // dense: workgroup = flat logit row r, output row r; gathered: workgroup =
   // gather record, output row = record index
   const int64_t o_row = blockIdx.x;
   const int item = a.gathered ? (int)blockIdx.x : a.row_item[blockIdx.x];
   const int64_t r = a.gathered ? a.rows[item].logit_row : (int64_t)blockIdx.x;
   if (a.gathered && a.row_index && tid == 0) a.row_index[item] = (int32_t)r;
-  u32x4* ov = reinterpret_cast<u32x4*>(reinterpret_cast<T*>(a.dlogits) + o_row * (int64_t)vocab);
+  T* out = reinterpret_cast<T*>(a.dlogits) + o_row * (int64_t)vocab;
+  const T* x = reinterpret_cast<const T*>(a.logits) + r * (int64_t)vocab;
+  int head = 0, nvec = vocab / N, n_extra = 0;  // vocab % N == 0 without EDGE
+  if constexpr (EDGE) {
+    const RowSplit<T> rs(x, vocab);
+    head = rs.head;
+    nvec = rs.nvec;
+    n_extra = rs.n_extra;
+  }
+  const int xi = tid < head ? tid : tid + nvec * N;  // this thread's head or tail element, if tid < n_extra
+  auto store = [&](int vi, const u32x4& v) {
+    if constexpr (EDGE) reinterpret_cast<Vec16Any<T>*>(out + head)[vi].v = v;
+    else __builtin_nontemporal_store(v, reinterpret_cast<u32x4*>(out) + vi);
+  };
   if (item < 0) {
 #pragma unroll
-    for (int j = 0; j < kLpbVecs; ++j) {
-      const int vi = j * kLpbThreads + tid;
-      if (vi < nvec) __builtin_nontemporal_store(u32x4{0, 0, 0, 0}, ov + vi);
+    for (int j = 0; j < R; ++j) {
+      const int vi = j * THREADS + tid;
+      if (vi < nvec) store(vi, u32x4{0, 0, 0, 0});
     }
+    if (EDGE && tid < n_extra) out[xi] = (T)0.f;
     return;
   }
-  const u32x4* xv = reinterpret_cast<const u32x4*>(reinterpret_cast<const T*>(a.logits) + r * (int64_t)vocab);
-  u32x4 u[kLpbVecs];
+  const u32x4* xv = reinterpret_cast<const u32x4*>(x + head);
+  u32x4 u[R];
 #pragma unroll
-  for (int j = 0; j < kLpbVecs; ++j) {
-    const int vi = j * kLpbThreads + tid;
+  for (int j = 0; j < R; ++j) {
+    const int vi = j * THREADS + tid;
     u[j] = vi < nvec ? __builtin_nontemporal_load(xv + vi) : u32x4{0, 0, 0, 0};
   }
+  float xe = kNegInf;
+  if (EDGE && tid < n_extra) xe = elem<T>(x, xi);
   const LogitRowItem it = a.rows[item];
   __shared__ int s_y[kMaxRowLabels];
   __shared__ float s_g[kMaxRowLabels];
@@ -374,7 +414,7 @@ __global__ __launch_bounds__(kLpbThreads) void logprob_bwd_reg_kernel(LogprobBwd
   const int cnt = it.label_cnt;
   if (tid == 0) s_bad = 0;
   __syncthreads();
-  for (int j = tid; j < cnt; j += kLpbThreads) {
+  for (int j = tid; j < cnt; j += THREADS) {
     const int32_t y = a.tokens[a.labels[it.label_off + j]];
     s_y[j] = y;
     s_g[j] = a.dseq[a.label_out[it.label_off + j]];
@@ -383,8 +423,8 @@ __global__ __launch_bounds__(kLpbThreads) void logprob_bwd_reg_kernel(LogprobBwd
   // logsumexp of the row from the registers
   float m = kNegInf;
 #pragma unroll
-  for (int j = 0; j < kLpbVecs; ++j) {
-    if (j * kLpbThreads + tid < nvec) {
+  for (int j = 0; j < R; ++j) {
+    if (j * THREADS + tid < nvec) {
       float f[N];
       Vec16<T>::unpack(u[j], f);
 #pragma unroll
@@ -398,8 +438,8 @@ __global__ __launch_bounds__(kLpbThreads) void logprob_bwd_reg_kernel(LogprobBwd
   if (m != kNegInf) {
     const float ml = m * kLog2e;
 #pragma unroll
-    for (int j = 0; j < kLpbVecs; ++j) {
-      if (j * kLpbThreads + tid < nvec) {
+    for (int j = 0; j < R; ++j) {
+      if (j * THREADS + tid < nvec) {
         float f[N];
         Vec16<T>::unpack(u[j], f);
 #pragma unroll
@@ -408,6 +448,7 @@ __global__ __launch_bounds__(kLpbThreads) void logprob_bwd_reg_kernel(LogprobBwd
     }
   }
   MaxSum acc = {m, s};
+  if (EDGE && tid < n_extra) acc = combine(acc, MaxSum{xe, 1.f});
   for (int off = 32; off > 0; off >>= 1) {
     MaxSum o;
     o.m = __shfl_xor(acc.m, off, 64);
@@ -434,15 +475,15 @@ __global__ __launch_bounds__(kLpbThreads) void logprob_bwd_reg_kernel(LogprobBwd
   const bool bad = s_bad != 0;
   opaque(u);
 #pragma unroll
-  for (int j = 0; j < kLpbVecs; ++j) {
-    const int vi = j * kLpbThreads + tid;
+  for (int j = 0; j < R; ++j) {
+    const int vi = j * THREADS + tid;
     if (vi < nvec) {
       float f[N];
       Vec16<T>::unpack(u[j], f);
 #pragma unroll
       for (int e = 0; e < N; ++e) f[e] = -c * fast_exp2(fmaf(f[e], kLog2e, -lse2));
       for (int l = 0; l < cnt; ++l) {
-        const int d = s_y[l] - vi * N;
+        const int d = s_y[l] - (head + vi * N);
         if ((unsigned)d < (unsigned)N) {
 #pragma unroll
           for (int e = 0; e < N; ++e) f[e] += (e == d) ? s_g[l] : 0.f;
@@ -452,8 +493,13 @@ __global__ __launch_bounds__(kLpbThreads) void logprob_bwd_reg_kernel(LogprobBwd
 #pragma unroll
         for (int e = 0; e < N; ++e) f[e] = __builtin_nanf("");
       }
-      __builtin_nontemporal_store(Pack16<T>::pack(f), ov + vi);
+      store(vi, Pack16<T>::pack(f));
     }
+  }
+  if (EDGE && tid < n_extra) {
+    float f = -c * fast_exp2(fmaf(xe, kLog2e, -lse2));
+    for (int l = 0; l < cnt; ++l) f += s_y[l] == xi ? s_g[l] : 0.f;
+    out[xi] = (T)(bad ? __builtin_nanf("") : f);
   }
 }
 
@@ -557,28 +603,41 @@ hipError_t launch_logprob(const LogprobLaunch& a, hipStream_t s) {
   return e;
 }
 
+namespace {
+
+// The shape with the most workgroups per compute unit whose registers hold a row
+// of `nvec` 16-byte vectors; the two-read kernel when none does.
+template <typename T, bool EDGE>
+void launch_logprob_bwd_rows(const LogprobBwdLaunch& a, int grid, int nvec, hipStream_t s) {
+  constexpr int kMost = EDGE ? 18 : 19;
+  if (nvec <= 512 * 8)
+    hipLaunchKernelGGL((logprob_bwd_reg_kernel<T, 512, 8, EDGE>), dim3(grid), dim3(512), 0, s, a);
+  else if (nvec <= 1024 * 8)
+    hipLaunchKernelGGL((logprob_bwd_reg_kernel<T, 1024, 8, EDGE>), dim3(grid), dim3(1024), 0, s, a);
+  else if (nvec <= 1024 * kMost)
+    hipLaunchKernelGGL((logprob_bwd_reg_kernel<T, 1024, kMost, EDGE>), dim3(grid), dim3(1024), 0, s, a);
+  else
+    hipLaunchKernelGGL(logprob_bwd_kernel<T>, dim3(grid), dim3(kLpThreads), 0, s, a);
+}
+
+}  // namespace
+
 hipError_t launch_logprob_bwd(const LogprobBwdLaunch& a, hipStream_t s) {
   const int grid = a.gathered ? a.n_rows : a.sumT;
   if (grid <= 0) return hipSuccess;
   TimingScope t(a.gathered ? "pp_logprob_bwd_rows" : "pp_logprob_bwd", s);
-  const int esz = a.dtype == kBF16 ? 2 : 4;
-  const int per_vec = 16 / esz;
-  // the one-read kernel needs every row to start on a 16-byte boundary and to
-  // fit in the workgroup's registers
-  const bool fits = a.vocab % per_vec == 0 && a.vocab <= kLpbThreads * kLpbVecs * per_vec &&
-                    (reinterpret_cast<uintptr_t>(a.logits) & 15) == 0 &&
-                    (reinterpret_cast<uintptr_t>(a.dlogits) & 15) == 0;
-  if (fits) {
-    if (a.dtype == kBF16)
-      hipLaunchKernelGGL(logprob_bwd_reg_kernel<__bf16>, dim3(grid), dim3(kLpbThreads), 0, s, a);
-    else
-      hipLaunchKernelGGL(logprob_bwd_reg_kernel<float>, dim3(grid), dim3(kLpbThreads), 0, s, a);
-    return hipGetLastError();
+  const int per_vec = a.dtype == kBF16 ? 8 : 4;
+  const int nvec = a.vocab / per_vec;
+  // every row of both matrices starts on a 16-byte boundary?
+  const bool edge = a.vocab % per_vec != 0 || (reinterpret_cast<uintptr_t>(a.logits) & 15) != 0 ||
+                    (reinterpret_cast<uintptr_t>(a.dlogits) & 15) != 0;
+  if (a.dtype == kBF16) {
+    if (edge) launch_logprob_bwd_rows<__bf16, true>(a, grid, nvec, s);
+    else launch_logprob_bwd_rows<__bf16, false>(a, grid, nvec, s);
+  } else {
+    if (edge) launch_logprob_bwd_rows<float, true>(a, grid, nvec, s);
+    else launch_logprob_bwd_rows<float, false>(a, grid, nvec, s);
   }
-  if (a.dtype == kBF16)
-    hipLaunchKernelGGL(logprob_bwd_kernel<__bf16>, dim3(grid), dim3(kLpThreads), 0, s, a);
-  else
-    hipLaunchKernelGGL(logprob_bwd_kernel<float>, dim3(grid), dim3(kLpThreads), 0, s, a);
   return hipGetLastError();
 }
 
