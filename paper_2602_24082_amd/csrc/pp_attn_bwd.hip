@@ -456,13 +456,18 @@ __global__ __launch_bounds__(512, 1) void bwd_dkdv_kernel(BwdParams<TO> p) {
 
 // Adds the partial sums of the cut key tiles, in slot order, and finishes them
 // as the dK/dV pass does a whole tile's.  A stream over the partials (64 MB for
-// one 8B-shaped row): a wave takes the accumulator blocks hm and hm + D/64 of 32
-// keys (the two that hold a rotary pair) and one gradient, and has two parts'
-// 1 KB runs in flight.
+// one 8B-shaped row), bound by how many loads are in flight: a wave takes four
+// consecutive accumulator registers of blocks hm and hm + D/64 of 32 keys (the
+// two that hold a rotary pair) and one gradient, and has up to four parts' 1 KB
+// runs of both in flight.  (With all sixteen registers to a wave and two parts in
+// flight a batch of few tiles kept a handful of workgroups busy: 1128
+// tokens of 2 kv-heads of size 64 took 16 us with the launch and take 9.)
 template <int D, typename TO, bool ROPE>
 __global__ __launch_bounds__(256) void bwd_kv_combine_kernel(BwdParams<TO> p) {
   constexpr int HM = D / 64;
   int b = blockIdx.x;
+  const int r4 = b & 3;
+  b >>= 2;
   const int hm = b % HM;
   b /= HM;
   const int g = b % p.hkv;
@@ -472,43 +477,49 @@ __global__ __launch_bounds__(256) void bwd_kv_combine_kernel(BwdParams<TO> p) {
   const int kb = threadIdx.x >> 6, lane = threadIdx.x & 63, hf = lane >> 5;
   const int j = sp.k0 + kb * 32 + (lane & 31);
   const int64_t stride = (int64_t)p.hkv * 2 * 4 * (32 * D);  // between slots
-  const float* part = p.kv_part + ((((int64_t)sp.slot0 * p.hkv + g) * 2 + pass) * 4 + kb) * (32 * D) + lane * 4;
-  f32x4 acc[2][4];
+  const float* part =
+      p.kv_part + ((((int64_t)sp.slot0 * p.hkv + g) * 2 + pass) * 4 + kb) * (32 * D) + (hm * 4 + r4) * 256 + lane * 4;
+  f32x4 g1 = f32x4{}, g2 = f32x4{};
+  constexpr int NP = 4;  // parts in flight
+  for (int i = 0; i < sp.parts; i += NP, part += NP * stride) {
+    f32x4 a[NP], c[NP];
 #pragma unroll
-  for (int h = 0; h < 2; ++h)
+    for (int n = 0; n < NP; ++n) {
+      if (i + n < sp.parts) {
+        a[n] = *reinterpret_cast<const f32x4*>(part + n * stride);
+        c[n] = *reinterpret_cast<const f32x4*>(part + n * stride + HM * 4 * 256);
+      }
+    }
 #pragma unroll
-    for (int r4 = 0; r4 < 4; ++r4) acc[h][r4] = f32x4{};
-#pragma unroll 2
-  for (int i = 0; i < sp.parts; ++i, part += stride)
-#pragma unroll
-    for (int h = 0; h < 2; ++h)
-#pragma unroll
-      for (int r4 = 0; r4 < 4; ++r4)
-        acc[h][r4] += *reinterpret_cast<const f32x4*>(part + ((hm + h * HM) * 4 + r4) * 256);
+    for (int n = 0; n < NP; ++n) {
+      if (i + n < sp.parts) {
+        g1 += a[n];
+        g2 += c[n];
+      }
+    }
+  }
   if (j >= sp.k_end) return;
   const int64_t krow = (int64_t)(sp.tok0 + j) * p.hkv + g;
   const float sc = pass == 0 ? p.scale : 1.f;
   TO* dst = (pass == 0 ? p.dk : p.dv) + krow * D;
+  g1 *= sc;
+  g2 *= sc;
+  const int c0 = 32 * hm + 8 * r4 + 4 * hf;
+  if constexpr (ROPE) {
+    if (pass == 0) {
+      const int pos = p.pos[sp.tok0 + j];
 #pragma unroll
-  for (int r4 = 0; r4 < 4; ++r4) {
-    f32x4 g1 = acc[0][r4] * sc, g2 = acc[1][r4] * sc;
-    const int c0 = 32 * hm + 8 * r4 + 4 * hf;
-    if constexpr (ROPE) {
-      if (pass == 0) {
-        const int pos = p.pos[sp.tok0 + j];
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          float cs, sn;
-          rope_cos_sin(pos, p.inv_freq[c0 + e], cs, sn);
-          const float u = g1[e], w = g2[e];
-          g1[e] = u * cs + w * sn;
-          g2[e] = w * cs - u * sn;
-        }
+      for (int e = 0; e < 4; ++e) {
+        float cs, sn;
+        rope_cos_sin(pos, p.inv_freq[c0 + e], cs, sn);
+        const float u = g1[e], w = g2[e];
+        g1[e] = u * cs + w * sn;
+        g2[e] = w * cs - u * sn;
       }
     }
-    store4<TO>(dst + c0, g1);
-    store4<TO>(dst + c0 + D / 2, g2);
   }
+  store4<TO>(dst + c0, g1);
+  store4<TO>(dst + c0 + D / 2, g2);
 }
 
 // ---------------------------------------------------------------------------
@@ -893,7 +904,7 @@ template <int D, typename TO>
 hipError_t launch_kv_combine(const AttnBwdLaunch& a, const BwdParams<TO>& p, hipStream_t s) {
   if (a.n_kv_splits == 0) return hipSuccess;
   TimingScope t("pp_attn_bwd_kv_combine", s);
-  const dim3 grid((unsigned)(a.n_kv_splits * 2 * a.hkv * (D / 64)));
+  const dim3 grid((unsigned)(a.n_kv_splits * 2 * a.hkv * (D / 64) * 4));
   if (a.rope) hipLaunchKernelGGL((bwd_kv_combine_kernel<D, TO, true>), grid, dim3(256), 0, s, p);
   else hipLaunchKernelGGL((bwd_kv_combine_kernel<D, TO, false>), grid, dim3(256), 0, s, p);
   return hipGetLastError();

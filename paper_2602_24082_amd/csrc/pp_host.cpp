@@ -285,14 +285,16 @@ inline int split_parts(int n, int most) { return most > 0 && n > most ? (n + mos
 
 // Finish time, in steps, of one kv-head's items (longest first, each tile cut
 // so that no part exceeds `most` steps; 0: none) on `units` compute units that
-// each take the next item when they are free.
-double kplan_span(const std::vector<KTileItem>& tiles, int most, int units) {
+// each take the next item when they are free, and the parts of cut tiles.
+double kplan_span(const std::vector<KTileItem>& tiles, int most, int units, int* n_parts) {
   // in steps of kBwdBlockM queries (2.0 us at head size 128, measured on 8B-shaped rows): 1.6 for a workgroup's K/V
-  // load and epilogue, 2 more for a part's fp32 sums and their addition
-  constexpr double kItem = 1.6, kPart = 2.0;
+  // load and epilogue, 1 more to write a part's fp32 sums
+  constexpr double kItem = 1.6, kPart = 1.0;
   std::vector<std::pair<int, bool>> items;  // steps, part of a cut tile
+  *n_parts = 0;
   for (const KTileItem& t : tiles) {
     const int n = t.n_end - t.n_begin, parts = split_parts(n, most);
+    if (parts > 1) *n_parts += parts;
     for (int i = 0; i < parts; ++i) items.emplace_back((int)((int64_t)n * (i + 1) / parts - (int64_t)n * i / parts), parts > 1);
   }
   std::stable_sort(items.begin(), items.end(), [](const auto& a, const auto& b) { return a.first > b.first; });
@@ -309,14 +311,19 @@ double kplan_span(const std::vector<KTileItem>& tiles, int most, int units) {
 
 // Cuts the longest key tiles of a batch that leaves compute units idle: with
 // few rows a prompt's first tile, which every later query of every head sees,
-// outlasts all others (one 8B-shaped row of 2080 tokens: 17 tiles x 8 kv-heads
-// on 256 units, the longest 132 steps against 37 a unit on average).  Batches of
+// outlasts all others (one 8B-shaped row of 2111 tokens: 17 tiles x 8 kv-heads
+// on 256 units, the longest 132 steps against 35 a unit on average).  Batches of
 // more than 2 workgroups a unit are left alone: cutting their tiles costs more
-// in the parts' fixed work than it evens out (measured 0 to 14% slower).  On that
-// row the pass took 201 us whole and takes 97 us cut, plus 16 us for the sums.  A cut
-// has to shorten the estimated span by a tenth and by the 3 steps of the extra
-// launch that adds the partial sums.
+// in the parts' fixed work than it evens out (measured 0 to 14% slower).  The
+// longest part allowed is the one of five that gives the smallest estimate: from
+// half as much again as the units' even share, which few tiles exceed, to a third
+// of it.  The estimate counts the launch that adds the partial sums and their
+// bytes at the 3 TB/s that launch reaches (46 parts of one kv-head a step).  A cut
+// has to shorten it by a tenth.  On that row the pass took 201 us whole and takes
+// 89 us cut (53 parts), plus 10 to 15 us for the sums; a rule of even shares, halves
+// and thirds of them took 101 us (67 parts).  One row of 4200 tokens: 324 -> 298 us.
 void split_kplan(int hkv, std::vector<KTileItem>* kv, std::vector<KTileSplit>* splits, int* slots) {
+  constexpr double kLaunch = 2.5, kPartsPerStep = 46.0;
   splits->clear();
   *slots = 0;
   if (kv->empty() || (int64_t)kv->size() * hkv > 2 * kComputeUnits) return;
@@ -325,12 +332,13 @@ void split_kplan(int hkv, std::vector<KTileItem>* kv, std::vector<KTileSplit>* s
   for (const KTileItem& t : *kv) work += t.n_end - t.n_begin;
   const int even = (int)((work + units - 1) / units);
   if ((*kv)[0].n_end < 8 || (*kv)[0].n_end <= even) return;  // the units' even share is the longer
-  const double whole = kplan_span(*kv, 0, units);
+  int parts = 0;
+  const double whole = kplan_span(*kv, 0, units, &parts);
   double best = whole;
   int most = 0;
-  for (int div = 1; div <= 3; ++div) {
-    const int m = std::max(4, (even + div - 1) / div);
-    const double s = kplan_span(*kv, m, units) + 3.0;
+  for (int sixths : {9, 6, 4, 3, 2}) {
+    const int m = std::max(4, (even * sixths + 5) / 6);
+    const double s = kplan_span(*kv, m, units, &parts) + kLaunch + (double)parts * hkv / kPartsPerStep;
     if (s < best) {
       best = s;
       most = m;
