@@ -945,9 +945,7 @@ hipError_t launch_bwd_t(const AttnBwdLaunch& a, hipStream_t s) {
   p.ds_tiles = a.ds_tiles;
   const int64_t n_rows = (int64_t)a.sumT * a.hq;
   if (n_rows == 0) return hipSuccess;
-  // the plan metadata (self-contained calls) lands before the first pass reads it
-  hipError_t e = a.stage_bytes ? launch_stage_copy(a.stage_src, a.stage_dst, a.stage_bytes, s) : hipSuccess;
-  if (e != hipSuccess) return e;
+  hipError_t e;
   if (a.ds) {
     {
       constexpr int RPB = 256 / (D / 8) * kPrepRowsPerThread;

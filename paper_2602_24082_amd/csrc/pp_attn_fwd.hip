@@ -270,17 +270,6 @@ __global__ __launch_bounds__(NW * 64, PP_FWD_MIN_WAVES) void attn_fwd_kernel(Fwd
     p.lse[(int64_t)head * p.sumT + it.tok0 + i] = l_tot > 0.f ? (m_ref + __log2f(l_tot)) * (1.0f / kLog2e) : 0.f;
 }
 
-__global__ __launch_bounds__(256) void to_bf16_kernel(const float* __restrict__ src, __bf16* __restrict__ dst,
-                                                      int64_t n) {
-  const int64_t i = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) * 4;
-  if (i + 4 <= n) {
-    const f32x4 v = *reinterpret_cast<const f32x4*>(src + i);
-    *reinterpret_cast<bf16x4*>(dst + i) = __builtin_convertvector(v, bf16x4);
-  } else {
-    for (int64_t j = i; j < n; ++j) dst[j] = (__bf16)src[j];
-  }
-}
-
 template <int D, typename TO>
 hipError_t launch_fwd_t(const AttnFwdLaunch& a, hipStream_t s) {
   FwdParams<TO> p;
@@ -313,14 +302,6 @@ hipError_t launch_fwd_t(const AttnFwdLaunch& a, hipStream_t s) {
 }
 
 }  // namespace
-
-hipError_t launch_to_bf16(const float* src, void* dst, int64_t n, hipStream_t s) {
-  if (n <= 0) return hipSuccess;
-  TimingScope t("pp_to_bf16", s);
-  const int64_t threads = (n + 3) / 4;
-  hipLaunchKernelGGL(to_bf16_kernel, dim3((unsigned)((threads + 255) / 256)), dim3(256), 0, s, src, (__bf16*)dst, n);
-  return hipGetLastError();
-}
 
 // q, k, v are bf16 here; a.dtype is the dtype of o.
 hipError_t launch_attn_fwd(const AttnFwdLaunch& a, hipStream_t s) {

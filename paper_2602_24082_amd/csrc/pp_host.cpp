@@ -647,8 +647,12 @@ pp_status stage_with(void* dst, const void* src, size_t bytes, hipStream_t strea
 pp_status stage_copy(void* dst, const void* src, size_t bytes, hipStream_t stream) {
   return stage_with(dst, src, bytes, stream, [&](const void* dev_src) -> pp_status {
     if (!dev_src) return PP_OK;
-    hipError_t e = launch_stage_copy(dev_src, dst, bytes, stream);
-    return e == hipSuccess ? PP_OK : hip_fail(e, "stage_copy_kernel");
+    StageLaunch a;
+    a.src = dev_src;
+    a.dst = dst;
+    a.bytes = bytes;
+    hipError_t e = launch_stage(a, stream);
+    return e == hipSuccess ? PP_OK : hip_fail(e, "stage_kernel");
   });
 }
 
@@ -1069,16 +1073,29 @@ void fwd_image(const Batch& bt, const FwdPlan& p, int head_dim, const double* ro
   }
 }
 
-// Enqueues the forward on metadata already staged in ws.
+// What precedes the passes: metadata still to be copied into ws, if any.
+StageLaunch stage_of(void* ws, const void* stage_src, size_t stage_bytes) {
+  StageLaunch a;
+  a.src = stage_src;
+  a.dst = ws;
+  a.bytes = stage_src ? stage_bytes : 0;
+  return a;
+}
+
+// Enqueues the forward on metadata already staged in ws, or (stage_src, mapped
+// pinned memory) copied there ahead of its kernels.
 pp_status fwd_launch(const FwdPlan& p, void* ws, int sumT, pp_dtype dtype, int hq, int hkv, int head_dim,
                      float scale, const void* q, const void* k, const void* v, void* o, float* lse,
-                     const RopeArgs* rope, hipStream_t s) {
+                     const RopeArgs* rope, hipStream_t s, const void* stage_src = nullptr, size_t stage_bytes = 0) {
   hipError_t e;
+  StageLaunch pre = stage_of(ws, stage_src, stage_bytes);
   const int32_t* d_pos = (const int32_t*)at(ws, p.lay, p.r_pos);
   const double* d_freq = (const double*)at(ws, p.lay, p.r_freq);
   if (rope) {
     // keys are rotated once, in the caller's dtype, into k_rot; the queries are
     // rotated inside the attention kernel
+    if ((e = launch_stage(pre, s)) != hipSuccess) return hip_fail(e, "stage_kernel");
+    pre = StageLaunch();
     RopeLaunch r{};
     r.x = k;
     r.y = rope->k_rot;
@@ -1097,14 +1114,14 @@ pp_status fwd_launch(const FwdPlan& p, void* ws, int sumT, pp_dtype dtype, int h
     void* qb = at(ws, p.lay, p.cast.q);
     void* kb = at(ws, p.lay, p.cast.k);
     void* vb = at(ws, p.lay, p.cast.v);
-    if ((e = launch_to_bf16((const float*)q, qb, (int64_t)sumT * hq * head_dim, s)) != hipSuccess ||
-        (e = launch_to_bf16((const float*)k, kb, (int64_t)sumT * hkv * head_dim, s)) != hipSuccess ||
-        (e = launch_to_bf16((const float*)v, vb, (int64_t)sumT * hkv * head_dim, s)) != hipSuccess)
-      return hip_fail(e, "fp32 to bf16 conversion launch");
+    pre.cast[0] = {(const float*)q, qb, (int64_t)sumT * hq * head_dim};
+    pre.cast[1] = {(const float*)k, kb, (int64_t)sumT * hkv * head_dim};
+    pre.cast[2] = {(const float*)v, vb, (int64_t)sumT * hkv * head_dim};
     q = qb;
     k = kb;
     v = vb;
   }
+  if ((e = launch_stage(pre, s)) != hipSuccess) return hip_fail(e, "stage_kernel");
   AttnFwdLaunch a{};
   a.q = q;
   a.k = k;
@@ -1155,8 +1172,10 @@ pp_status attn_fwd_impl(const pp_pack_desc* desc, pp_dtype dtype, int hq, int hk
   const double base = rope ? rope->base : 0.0;
   fwd_image(bt, p, head_dim, rope ? &base : nullptr, &img);
   hipStream_t s = (hipStream_t)hip_stream;
-  if ((st = stage_copy(ws, img.buf.data(), img.buf.size(), s)) != PP_OK) return st;
-  return fwd_launch(p, ws, bt.sumT, dtype, hq, hkv, head_dim, scale, q, k, v, o, lse, rope, s);
+  return stage_with(ws, img.buf.data(), img.buf.size(), s, [&](const void* dev_src) {
+    return fwd_launch(p, ws, bt.sumT, dtype, hq, hkv, head_dim, scale, q, k, v, o, lse, rope, s, dev_src,
+                      img.buf.size());
+  });
 }
 
 }  // namespace
@@ -1209,30 +1228,30 @@ void bwd_image(const Batch& bt, const BwdPlan& p, int head_dim, const double* ro
   }
 }
 
-// Enqueues the backward on metadata already staged in ws.
-// stage_src / stage_bytes: metadata still to be copied into ws (a copy kernel
-// ahead of the backward's passes), or null.
+// Enqueues the backward on metadata already staged in ws, or (stage_src, mapped
+// pinned memory) copied there ahead of its kernels.
 pp_status bwd_launch(const BwdPlan& p, void* ws, int sumT, pp_dtype dtype, int hq, int hkv, int head_dim,
                      float scale, const void* q, const void* k, const void* v, const void* o,
                      const float* lse, const void* dout, void* dq, void* dk, void* dv, bool rope, bool store_ds,
                      hipStream_t s, const void* stage_src = nullptr, size_t stage_bytes = 0) {
   hipError_t e;
+  StageLaunch pre = stage_of(ws, stage_src, stage_bytes);
   const void* dout_bf = dout;
   if (p.cast.on) {
     void* qb = at(ws, p.lay, p.cast.q);
     void* kb = at(ws, p.lay, p.cast.k);
     void* vb = at(ws, p.lay, p.cast.v);
     void* db = at(ws, p.lay, p.cast.dout);
-    if ((e = launch_to_bf16((const float*)q, qb, (int64_t)sumT * hq * head_dim, s)) != hipSuccess ||
-        (e = launch_to_bf16((const float*)k, kb, (int64_t)sumT * hkv * head_dim, s)) != hipSuccess ||
-        (e = launch_to_bf16((const float*)v, vb, (int64_t)sumT * hkv * head_dim, s)) != hipSuccess ||
-        (e = launch_to_bf16((const float*)dout, db, (int64_t)sumT * hq * head_dim, s)) != hipSuccess)
-      return hip_fail(e, "fp32 to bf16 conversion launch");
+    pre.cast[0] = {(const float*)q, qb, (int64_t)sumT * hq * head_dim};
+    pre.cast[1] = {(const float*)k, kb, (int64_t)sumT * hkv * head_dim};
+    pre.cast[2] = {(const float*)v, vb, (int64_t)sumT * hkv * head_dim};
+    pre.cast[3] = {(const float*)dout, db, (int64_t)sumT * hq * head_dim};
     q = qb;
     k = kb;
     v = vb;
     dout_bf = db;
   }
+  if ((e = launch_stage(pre, s)) != hipSuccess) return hip_fail(e, "stage_kernel");
   AttnBwdLaunch a{};
   a.q = q;
   a.k = k;
@@ -1273,9 +1292,6 @@ pp_status bwd_launch(const BwdPlan& p, void* ws, int sumT, pp_dtype dtype, int h
     a.kb_panel = (const DsPanel*)at(ws, p.lay, p.r_panels);
     a.ds_tiles = p.ds_tiles;
   }
-  a.stage_src = stage_src;
-  a.stage_dst = ws;
-  a.stage_bytes = stage_src ? stage_bytes : 0;
   e = launch_attn_bwd(a, s);
   if (e != hipSuccess) return hip_fail(e, "attention backward launch");
   return PP_OK;
@@ -1307,7 +1323,6 @@ pp_status attn_bwd_impl(const pp_pack_desc* desc, pp_dtype dtype, int hq, int hk
   const double base = rope_base ? *rope_base : 0.0;
   bwd_image(bt, p, head_dim, rope_base ? &base : nullptr, &img);
   hipStream_t s = (hipStream_t)hip_stream;
-  // the metadata copy is enqueued by the backward's launcher, ahead of its passes
   return stage_with(ws, img.buf.data(), img.buf.size(), s, [&](const void* dev_src) {
     return bwd_launch(p, ws, bt.sumT, dtype, hq, hkv, head_dim, scale, q, k, v, o, lse, dout, dq, dk, dv,
                       rope_base != nullptr, store_ds, s, dev_src, img.buf.size());
@@ -1577,12 +1592,10 @@ pp_status pp_seq_logprob(const pp_pack_desc* desc, pp_dtype logits_dtype, int vo
   img.put(p.lay.regions[p.r_rows], p.l.rows.data(), p.l.rows.size() * sizeof(LogitRowItem));
   img.put(p.lay.regions[p.r_labels], p.l.labels.data(), p.l.labels.size() * 4);
   img.put(p.lay.regions[p.r_resp], p.l.resp.data(), p.l.resp.size() * sizeof(RespItem));
-  if ((st = stage_copy(ws, img.buf.data(), img.buf.size(), s)) != PP_OK) return st;
   LogprobLaunch a{};
   a.logits = logits;
   a.tokens = tokens;
   a.tok = tok_logp ? tok_logp : (float*)at(ws, p.lay, p.r_tok);
-  a.zero_tok = tok_logp != nullptr;
   a.seq = seq_logp;
   a.rows = (const LogitRowItem*)at(ws, p.lay, p.r_rows);
   a.labels = (const int32_t*)at(ws, p.lay, p.r_labels);
@@ -1592,9 +1605,19 @@ pp_status pp_seq_logprob(const pp_pack_desc* desc, pp_dtype logits_dtype, int vo
   a.vocab = vocab;
   a.sumT = bt.sumT;
   a.dtype = logits_dtype == PP_FP32 ? kFP32 : kBF16;
-  hipError_t e = launch_logprob(a, s);
-  if (e != hipSuccess) return hip_fail(e, "logprob launch");
-  return PP_OK;
+  return stage_with(ws, img.buf.data(), img.buf.size(), s, [&](const void* dev_src) -> pp_status {
+    StageLaunch pre = stage_of(ws, dev_src, img.buf.size());
+    if (tok_logp) {
+      // the caller's per-token output reads 0 off the responses; workspace scratch
+      // is only read back at response positions, so it is not cleared
+      pre.zero = tok_logp;
+      pre.n_zero = bt.sumT;
+    }
+    hipError_t e = launch_stage(pre, s);
+    if (e != hipSuccess) return hip_fail(e, "stage_kernel");
+    e = launch_logprob(a, s);
+    return e == hipSuccess ? PP_OK : hip_fail(e, "logprob launch");
+  });
 }
 
 }  // extern "C"

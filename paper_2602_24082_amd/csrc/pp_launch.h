@@ -29,12 +29,25 @@ struct TimingScope {
   hipEvent_t stop_ = nullptr;
 };
 
-// Copies `bytes` from src (the device address of mapped pinned host memory) to
-// device memory dst on stream s; both 16-byte aligned.
-hipError_t launch_stage_copy(const void* src, void* dst, size_t bytes, hipStream_t s);
-
-// fp32 -> bf16 (round to nearest even) copy, for fp32 callers of attention.
-hipError_t launch_to_bf16(const float* src, void* dst, int64_t n, hipStream_t s);
+// What precedes a call's kernels, in one launch; parts of size 0 are left out.
+constexpr int kStageCasts = 4;
+struct StageLaunch {
+  // plan metadata from src (the device address of mapped pinned host memory) to
+  // device memory dst, both 16-byte aligned
+  const void* src = nullptr;
+  void* dst = nullptr;
+  size_t bytes = 0;
+  // fp32 -> bf16 (round to nearest even) copies; src and dst 16-byte aligned
+  struct Cast {
+    const float* src = nullptr;
+    void* dst = nullptr;
+    int64_t n = 0;
+  } cast[kStageCasts];
+  // n_zero floats set to 0
+  float* zero = nullptr;
+  int64_t n_zero = 0;
+};
+hipError_t launch_stage(const StageLaunch& a, hipStream_t s);
 
 // q, k, v are bf16; o has dtype `dtype`.
 struct AttnFwdLaunch {
@@ -104,11 +117,6 @@ struct AttnBwdLaunch {
   const int32_t* row_kb0 = nullptr;
   const DsPanel* kb_panel = nullptr;
   int64_t ds_tiles = 0;
-  // plan metadata to copy into stage_dst (16-byte aligned) from mapped pinned
-  // host memory ahead of the backward's first pass; none if 0 bytes
-  const void* stage_src = nullptr;
-  void* stage_dst = nullptr;
-  size_t stage_bytes = 0;
 };
 hipError_t launch_attn_bwd(const AttnBwdLaunch& a, hipStream_t s);
 
@@ -128,7 +136,7 @@ hipError_t launch_rope(const RopeLaunch& a, hipStream_t s);
 struct LogprobLaunch {
   const void* logits;
   const int32_t* tokens;
-  float* tok;                // [sumT]; response positions written (zero-filled first if zero_tok)
+  float* tok;                // [sumT]; response positions written
   float* seq;                // [B * K_max]
   const LogitRowItem* rows;
   const int32_t* labels;     // flat token positions
@@ -138,9 +146,6 @@ struct LogprobLaunch {
   int vocab;
   int sumT;
   int dtype;
-  // the caller's per-token output, whose other positions must read 0; workspace
-  // scratch is only read back at response positions, so it is not cleared
-  bool zero_tok;
 };
 hipError_t launch_logprob(const LogprobLaunch& a, hipStream_t s);
 

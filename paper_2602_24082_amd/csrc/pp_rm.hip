@@ -8,13 +8,14 @@
 //
 //   rm_scores      one workgroup per slot: w . h_row + bias (fixed-order
 //                  reduction; 0 for slots without a row)
-//   rm_dhidden     one workgroup per flat row: (sum of the slots' dscores) * w
-//                  on the rows some slot reads, 0 everywhere else
-//   rm_dw          one thread per column: dw = sum over slots, in slot order,
-//                  of dscore * h_row; thread 0 also sums dbias
+//   rm_bwd         its first workgroups: dw = sum over slots, in slot order, of
+//                  dscore * h_row (one thread per column), and one for dbias, the
+//                  sum of the dscores; then one workgroup per flat row: dhidden = (sum of the
+//                  slots' dscores) * w on the rows some slot reads, 0 elsewhere
 //
-// All three are tiny next to attention (B*K rows of the hidden matrix); the
-// dhidden pass writes the whole [sumT, H] gradient once.
+// The backward is bound by writing the [sumT, H] gradient once.  dw reads only
+// the slots' rows but as a chain over them, so it runs beside that write in one
+// launch (17792 rows of 4096 bf16, 32 slots: 22 us + 14 us apart, 23 us together).
 
 #include <hip/hip_runtime.h>
 
@@ -31,6 +32,17 @@ __device__ __forceinline__ float ld(const T* p, int64_t i) {
   return (float)p[i];
 }
 
+// 16 bytes of T, and whether rows of H elements from `p` on start on 16-byte boundaries.
+template <typename T>
+struct Vec {
+  static constexpr int N = 16 / (int)sizeof(T);
+  typedef T type __attribute__((ext_vector_type(N)));
+};
+template <typename T>
+__device__ __forceinline__ bool rows_aligned(const void* p, int H) {
+  return H % Vec<T>::N == 0 && (reinterpret_cast<uintptr_t>(p) & 15) == 0;
+}
+
 template <typename T>
 __global__ __launch_bounds__(kRmThreads) void rm_scores_kernel(RmLaunch a) {
   const int slot = blockIdx.x;
@@ -40,7 +52,19 @@ __global__ __launch_bounds__(kRmThreads) void rm_scores_kernel(RmLaunch a) {
   if (row >= 0) {
     const T* h = reinterpret_cast<const T*>(a.hidden) + row * (int64_t)a.H;
     const T* w = reinterpret_cast<const T*>(a.w);
-    for (int i = tid; i < a.H; i += kRmThreads) acc = fmaf(ld<T>(h, i), ld<T>(w, i), acc);
+    if (rows_aligned<T>(a.hidden, a.H) && rows_aligned<T>(a.w, a.H)) {
+      using V = typename Vec<T>::type;
+      const V* hv = reinterpret_cast<const V*>(h);
+      const V* wv = reinterpret_cast<const V*>(w);
+#pragma unroll 2
+      for (int i = tid; i < a.H / Vec<T>::N; i += kRmThreads) {
+        const V x = hv[i], y = wv[i];
+#pragma unroll
+        for (int e = 0; e < Vec<T>::N; ++e) acc = fmaf((float)x[e], (float)y[e], acc);
+      }
+    } else {
+      for (int i = tid; i < a.H; i += kRmThreads) acc = fmaf(ld<T>(h, i), ld<T>(w, i), acc);
+    }
   }
   acc = wave_sum(acc);
   __shared__ float part[kRmThreads / 64];
@@ -54,8 +78,7 @@ __global__ __launch_bounds__(kRmThreads) void rm_scores_kernel(RmLaunch a) {
 }
 
 template <typename T>
-__global__ __launch_bounds__(kRmThreads) void rm_dhidden_kernel(RmBwdLaunch a) {
-  const int64_t r = blockIdx.x;
+__device__ __forceinline__ void rm_dhidden_row(const RmBwdLaunch& a, int64_t r) {
   const int rec = a.row_rec[r];
   float g = 0.f;
   if (rec >= 0) {
@@ -64,26 +87,76 @@ __global__ __launch_bounds__(kRmThreads) void rm_dhidden_kernel(RmBwdLaunch a) {
   }
   T* out = reinterpret_cast<T*>(a.dhidden) + r * (int64_t)a.H;
   const T* w = reinterpret_cast<const T*>(a.w);
+  if (rows_aligned<T>(a.dhidden, a.H) && rows_aligned<T>(a.w, a.H)) {
+    using V = typename Vec<T>::type;
+    for (int i = threadIdx.x; i < a.H / Vec<T>::N; i += kRmThreads) {
+      V y = {};
+      if (rec >= 0) {
+        const V x = reinterpret_cast<const V*>(w)[i];
+#pragma unroll
+        for (int e = 0; e < Vec<T>::N; ++e) y[e] = (T)(g * (float)x[e]);
+      }
+      reinterpret_cast<V*>(out)[i] = y;
+    }
+    return;
+  }
   for (int i = threadIdx.x; i < a.H; i += kRmThreads) out[i] = (T)(rec >= 0 ? g * ld<T>(w, i) : 0.f);
 }
 
+// The slots' records come 64 at a time, one a lane, and 32 slots' elements are in
+// flight at once: every further round of loads waits behind dhidden's stores.
 template <typename T>
-__global__ __launch_bounds__(kRmThreads) void rm_dw_kernel(RmBwdLaunch a) {
-  const int i = blockIdx.x * kRmThreads + threadIdx.x;
-  if (i < a.H) {
-    float acc = 0.f;
-    for (int s = 0; s < a.n_slots; ++s) {
-      const int64_t row = a.slot_row[s];
-      if (row >= 0) acc = fmaf(a.dscores[s], ld<T>(reinterpret_cast<const T*>(a.hidden), row * (int64_t)a.H + i), acc);
+__device__ __forceinline__ void rm_dw_columns(const RmBwdLaunch& a, int block) {
+  const int lane = threadIdx.x & 63;
+  const int i = min(block * kRmThreads + (int)threadIdx.x, a.H - 1);
+  constexpr int S = 32;
+  const T* h = reinterpret_cast<const T*>(a.hidden) + i;
+  float acc = 0.f;
+  for (int s0 = 0; s0 < a.n_slots; s0 += 64) {
+    const int n = min(64, a.n_slots - s0);
+    const int row_l = lane < n ? (int)a.slot_row[s0 + lane] : -1;  // flat rows fit 31 bits
+    const float g_l = lane < n ? a.dscores[s0 + lane] : 0.f;
+    for (int j0 = 0; j0 < n; j0 += S) {
+      float x[S];
+#pragma unroll
+      for (int j = 0; j < S; ++j) {
+        const int row = __builtin_amdgcn_readlane(row_l, j0 + j);
+        if (row >= 0) x[j] = ld<T>(h, row * (int64_t)a.H);
+      }
+#pragma unroll
+      for (int j = 0; j < S; ++j) {
+        const float g = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(g_l), j0 + j));
+        if (__builtin_amdgcn_readlane(row_l, j0 + j) >= 0) acc = fmaf(g, x[j], acc);
+      }
     }
-    a.dw[i] = acc;
   }
-  if (i == 0 && a.dbias) {
-    float b = 0.f;
-    for (int s = 0; s < a.n_slots; ++s)
-      if (a.slot_row[s] >= 0) b += a.dscores[s];
-    *a.dbias = b;
+  if (block * kRmThreads + (int)threadIdx.x < a.H) a.dw[i] = acc;
+}
+
+// dbias = the sum of dscores in slot order: a wave loads 64 at a time (a load per
+// addition would take longer than all of dhidden)
+__device__ __forceinline__ void rm_dbias(const RmBwdLaunch& a) {
+  if (!a.dbias || threadIdx.x >= 64) return;
+  float b = 0.f;
+  for (int s0 = 0; s0 < a.n_slots; s0 += 64) {
+    const int s = s0 + (int)threadIdx.x;
+    const bool on = s < a.n_slots && a.slot_row[s] >= 0;
+    const float v = on ? a.dscores[s] : 0.f;
+    const uint64_t mask = __ballot(on);
+    for (int j = 0; j < 64; ++j) {
+      const float x = __shfl(v, j, 64);
+      if ((mask >> j) & 1) b += x;
+    }
   }
+  if (threadIdx.x == 0) *a.dbias = b;
+}
+
+template <typename T>
+__global__ __launch_bounds__(kRmThreads) void rm_bwd_kernel(RmBwdLaunch a, int dw_blocks) {
+  const int b = blockIdx.x;
+  if (b < dw_blocks) rm_dw_columns<T>(a, b);
+  else if (b == dw_blocks) rm_dbias(a);
+  else rm_dhidden_row<T>(a, b - dw_blocks - 1);
 }
 
 }  // namespace
@@ -99,21 +172,13 @@ hipError_t launch_rm_scores(const RmLaunch& a, hipStream_t s) {
 }
 
 hipError_t launch_rm_bwd(const RmBwdLaunch& a, hipStream_t s) {
-  if (a.sumT > 0) {
-    TimingScope t("pp_rm_dhidden", s);
-    if (a.dtype == kBF16)
-      hipLaunchKernelGGL(rm_dhidden_kernel<__bf16>, dim3(a.sumT), dim3(kRmThreads), 0, s, a);
-    else
-      hipLaunchKernelGGL(rm_dhidden_kernel<float>, dim3(a.sumT), dim3(kRmThreads), 0, s, a);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-  }
-  TimingScope t("pp_rm_dw", s);
-  const int blocks = (a.H + kRmThreads - 1) / kRmThreads;
+  TimingScope t("pp_rm_dhidden", s);
+  const int dw_blocks = (a.H + kRmThreads - 1) / kRmThreads;
+  const dim3 grid((unsigned)(dw_blocks + 1 + a.sumT));
   if (a.dtype == kBF16)
-    hipLaunchKernelGGL(rm_dw_kernel<__bf16>, dim3(blocks), dim3(kRmThreads), 0, s, a);
+    hipLaunchKernelGGL(rm_bwd_kernel<__bf16>, grid, dim3(kRmThreads), 0, s, a, dw_blocks);
   else
-    hipLaunchKernelGGL(rm_dw_kernel<float>, dim3(blocks), dim3(kRmThreads), 0, s, a);
+    hipLaunchKernelGGL(rm_bwd_kernel<float>, grid, dim3(kRmThreads), 0, s, a, dw_blocks);
   return hipGetLastError();
 }
 

@@ -1,11 +1,17 @@
-// Plan-metadata staging on the caller's stream.  The host writes the metadata
-// image into mapped pinned host memory; this kernel copies it into the
-// workspace.  Staying on the compute queue, the copy needs no hand-off to a DMA
-// engine and back, which for an image of a few hundred KB costs more than the
-// copy itself.
+// What a call needs on its stream before its own kernels, in one launch:
+//   * plan metadata, which the host wrote into mapped pinned memory, copied into
+//     the workspace (on the compute queue the copy needs no hand-off to a DMA
+//     engine and back, which for an image of a few hundred KB costs more than the
+//     copy itself);
+//   * bf16 copies (round to nearest even) of fp32 attention inputs;
+//   * zeros in the positions of an output that the kernels do not write.
+// Each piece is a few us of memory traffic, so what a small call pays is the
+// launches: an fp32 forward and backward of 761 tokens (four heads of size 64)
+// enqueued seven conversions and two copies of 2 us each, and now two launches.
 
 #include <hip/hip_runtime.h>
 
+#include "pp_device.h"
 #include "pp_launch.h"
 
 namespace pp {
@@ -13,25 +19,63 @@ namespace {
 
 typedef uint32_t Chunk16 __attribute__((ext_vector_type(4)));
 
-// Bytes [0, 16 n16) move as 16-byte vectors, the last `tail` (< 16) one by one.
-__global__ __launch_bounds__(256) void stage_copy_kernel(const Chunk16* __restrict__ src, Chunk16* __restrict__ dst,
-                                                         int64_t n16, int tail) {
-  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (i < n16) dst[i] = src[i];
-  if (i < tail)
-    reinterpret_cast<uint8_t*>(dst + n16)[i] = reinterpret_cast<const uint8_t*>(src + n16)[i];
+constexpr int kThreads = 256;
+
+// Work of the launch's blocks: the copy's first, then each conversion's, then the zeros'.
+struct StageBlocks {
+  int copy;
+  int cast[kStageCasts];
+  int zero;
+};
+
+__global__ __launch_bounds__(kThreads) void stage_kernel(StageLaunch a, StageBlocks nb) {
+  int b = blockIdx.x;
+  if (b < nb.copy) {
+    // bytes [0, 16 n16) move as 16-byte vectors, the last few (< 16) one by one
+    const int64_t n16 = (int64_t)(a.bytes / 16);
+    const int tail = (int)(a.bytes % 16);
+    const Chunk16* src = static_cast<const Chunk16*>(a.src);
+    Chunk16* dst = static_cast<Chunk16*>(a.dst);
+    const int64_t i = (int64_t)b * kThreads + threadIdx.x;
+    if (i < n16) dst[i] = src[i];
+    if (i < tail) reinterpret_cast<uint8_t*>(dst + n16)[i] = reinterpret_cast<const uint8_t*>(src + n16)[i];
+    return;
+  }
+  b -= nb.copy;
+#pragma unroll
+  for (int c = 0; c < kStageCasts; ++c) {
+    if (b < nb.cast[c]) {
+      const float* src = a.cast[c].src;
+      __bf16* dst = static_cast<__bf16*>(a.cast[c].dst);
+      const int64_t n = a.cast[c].n;
+      const int64_t i = ((int64_t)b * kThreads + threadIdx.x) * 4;
+      if (i + 4 <= n) {
+        const f32x4 v = *reinterpret_cast<const f32x4*>(src + i);
+        *reinterpret_cast<bf16x4*>(dst + i) = __builtin_convertvector(v, bf16x4);
+      } else {
+        for (int64_t j = i; j < n; ++j) dst[j] = (__bf16)src[j];
+      }
+      return;
+    }
+    b -= nb.cast[c];
+  }
+  const int64_t i = (int64_t)b * kThreads + threadIdx.x;
+  if (i < a.n_zero) a.zero[i] = 0.f;
 }
 
 }  // namespace
 
-hipError_t launch_stage_copy(const void* src, void* dst, size_t bytes, hipStream_t s) {
-  if (bytes == 0) return hipSuccess;
-  TimingScope t("pp_stage", s);
-  const int64_t n16 = (int64_t)(bytes / 16);
-  const int tail = (int)(bytes % 16);
-  const int64_t threads = n16 > tail ? n16 : tail;
-  hipLaunchKernelGGL(stage_copy_kernel, dim3((unsigned)((threads + 255) / 256)), dim3(256), 0, s,
-                     static_cast<const Chunk16*>(src), static_cast<Chunk16*>(dst), n16, tail);
+hipError_t launch_stage(const StageLaunch& a, hipStream_t s) {
+  auto blocks = [](int64_t threads) { return (int)((threads + kThreads - 1) / kThreads); };
+  const int64_t n16 = (int64_t)(a.bytes / 16), tail = (int64_t)(a.bytes % 16);
+  StageBlocks nb{};
+  nb.copy = blocks(n16 > tail ? n16 : tail);
+  int64_t total = nb.copy;
+  for (int c = 0; c < kStageCasts; ++c) total += nb.cast[c] = blocks((a.cast[c].n + 3) / 4);
+  total += nb.zero = blocks(a.n_zero);
+  if (total == 0) return hipSuccess;
+  TimingScope t(nb.copy ? "pp_stage" : "pp_to_bf16", s);
+  hipLaunchKernelGGL(stage_kernel, dim3((unsigned)total), dim3(kThreads), 0, s, a, nb);
   return hipGetLastError();
 }
 
