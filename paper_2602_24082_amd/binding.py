@@ -203,7 +203,11 @@ def pp_workspace_size(pack: Pack, hq: int = 1, hkv: int = 1, head_dim: int = 64,
                       fwd=True, bwd=True, logprob=False, loss=True, dtype: int = PP_BF16):
     """Workspace bytes (fwd, bwd, logprob, loss); entries not asked for are None.
     dtype is the attention input dtype code (PP_BF16 or PP_FP32)."""
-    h = _desc_of(pack)
+    return _workspace_sizes(_desc_of(pack), hq, hkv, head_dim, vocab, fwd, bwd, logprob, loss, dtype)
+
+
+def _workspace_sizes(h: _DescHolder, hq=1, hkv=1, head_dim=64, vocab=0, fwd=False, bwd=False, logprob=False, loss=False,
+                     dtype=PP_BF16):
     vals = [ctypes.c_size_t(0) for _ in range(4)]
     want = [fwd, bwd, logprob, loss]
     args = [ctypes.byref(v) if w else None for v, w in zip(vals, want)]
@@ -213,16 +217,19 @@ def pp_workspace_size(pack: Pack, hq: int = 1, hkv: int = 1, head_dim: int = 64,
 
 def pp_bwd_stored_ds_workspace_size(pack: Pack, hq: int, hkv: int, head_dim: int, dtype: int = PP_BF16):
     """(bwd, plan) workspace bytes that select the backward's stored-dS mode."""
-    h = _desc_of(pack)
+    return _stored_ds_sizes(_desc_of(pack), hq, hkv, head_dim, dtype)
+
+
+def _stored_ds_sizes(h: _DescHolder, hq, hkv, head_dim, dtype):
     b, p = ctypes.c_size_t(0), ctypes.c_size_t(0)
     _check(lib().pp_bwd_stored_ds_workspace_size(h.ref, dtype, hq, hkv, head_dim, ctypes.byref(b), ctypes.byref(p)))
     return int(b.value), int(p.value)
 
 
-def _bwd_workspace_bytes(pack: Pack, hq: int, hkv: int, d: int, dtype: int, store_ds: bool) -> int:
+def _bwd_workspace_bytes(h: _DescHolder, hq: int, hkv: int, d: int, dtype: int, store_ds: bool) -> int:
     if store_ds:
-        return pp_bwd_stored_ds_workspace_size(pack, hq, hkv, d, dtype)[0]
-    return pp_workspace_size(pack, hq, hkv, d, fwd=False, bwd=True, loss=False, dtype=dtype)[1]
+        return _stored_ds_sizes(h, hq, hkv, d, dtype)[0]
+    return _workspace_sizes(h, hq, hkv, d, bwd=True, dtype=dtype)[1]
 
 
 def pp_attn_fwd(pack: Pack, q: torch.Tensor, k: torch.Tensor, v: torch.Tensor, scale: float = 0.0,
@@ -237,7 +244,7 @@ def pp_attn_fwd(pack: Pack, q: torch.Tensor, k: torch.Tensor, v: torch.Tensor, s
     if lse is None:
         lse = torch.empty(hq, T, dtype=torch.float32, device=q.device)
     if ws is None:
-        nb, = pp_workspace_size(pack, hq, hkv, d, fwd=True, bwd=False, loss=False, dtype=_dtype_code(q))[:1]
+        nb = _workspace_sizes(h, hq, hkv, d, fwd=True, dtype=_dtype_code(q))[0]
         ws = _workspace(nb, q.device)
     _check(lib().pp_attn_fwd(h.ref, _dtype_code(q), hq, hkv, d, float(scale), _ptr(q), _ptr(k), _ptr(v),
                              _ptr(out), _ptr(lse), _ptr(ws), ws.numel(), _stream(q.device)))
@@ -256,7 +263,7 @@ def pp_attn_bwd(pack: Pack, q, k, v, o, lse, dout, scale: float = 0.0, dq=None, 
     dk = torch.empty_like(k) if dk is None else dk
     dv = torch.empty_like(v) if dv is None else dv
     if ws is None:
-        ws = _workspace(_bwd_workspace_bytes(pack, hq, hkv, d, _dtype_code(q), store_ds), q.device)
+        ws = _workspace(_bwd_workspace_bytes(h, hq, hkv, d, _dtype_code(q), store_ds), q.device)
     _check(lib().pp_attn_bwd(h.ref, _dtype_code(q), hq, hkv, d, float(scale), _ptr(q), _ptr(k), _ptr(v),
                              _ptr(o), _ptr(lse), _ptr(dout), _ptr(dq), _ptr(dk), _ptr(dv), _ptr(ws),
                              ws.numel(), _stream(q.device)))
@@ -313,7 +320,7 @@ def pp_attn_fwd_rope(pack: Pack, q, k, v, rope_base: float, scale: float = 0.0, 
         q_rot = torch.empty_like(q)
     k_rot = torch.empty_like(k) if k_rot is None else k_rot
     if ws is None:
-        nb = pp_workspace_size(pack, hq, hkv, d, fwd=True, bwd=False, loss=False, dtype=_dtype_code(q))[0]
+        nb = _workspace_sizes(h, hq, hkv, d, fwd=True, dtype=_dtype_code(q))[0]
         ws = _workspace(nb, q.device)
     _check(lib().pp_attn_fwd_rope(h.ref, _dtype_code(q), hq, hkv, d, float(scale), float(rope_base), _ptr(q),
                                   _ptr(k), _ptr(v), _ptr(out), _ptr(lse), _ptr(q_rot), _ptr(k_rot), _ptr(ws),
@@ -332,7 +339,7 @@ def pp_attn_bwd_rope(pack: Pack, q_rot, k_rot, v, o, lse, dout, rope_base: float
     dk = torch.empty_like(k_rot) if dk is None else dk
     dv = torch.empty_like(v) if dv is None else dv
     if ws is None:
-        ws = _workspace(_bwd_workspace_bytes(pack, hq, hkv, d, _dtype_code(q_rot), store_ds), q_rot.device)
+        ws = _workspace(_bwd_workspace_bytes(h, hq, hkv, d, _dtype_code(q_rot), store_ds), q_rot.device)
     _check(lib().pp_attn_bwd_rope(h.ref, _dtype_code(q_rot), hq, hkv, d, float(scale), float(rope_base),
                                   _ptr(q_rot), _ptr(k_rot), _ptr(v), _ptr(o), _ptr(lse), _ptr(dout), _ptr(dq),
                                   _ptr(dk), _ptr(dv), _ptr(ws), ws.numel(), _stream(q_rot.device)))
@@ -419,7 +426,7 @@ def pp_seq_logprob(pack: Pack, logits: torch.Tensor, tokens: torch.Tensor, want_
     if want_tok and tok is None:
         tok = torch.empty(logits.shape[0], dtype=torch.float32, device=dev)
     if ws is None:
-        nb = pp_workspace_size(pack, vocab=V, fwd=False, bwd=False, logprob=True, loss=False)[2]
+        nb = _workspace_sizes(h, vocab=V, logprob=True)[2]
         ws = _workspace(nb, dev)
     if tokens.dtype != torch.int32:
         raise TypeError("tokens must be int32")
@@ -437,7 +444,7 @@ def pp_seq_logprob_bwd(pack: Pack, logits: torch.Tensor, tokens: torch.Tensor, d
     if dlogits is None:
         dlogits = torch.empty_like(logits)
     if ws is None:
-        nb = pp_workspace_size(pack, vocab=V, fwd=False, bwd=False, logprob=True, loss=False)[2]
+        nb = _workspace_sizes(h, vocab=V, logprob=True)[2]
         ws = _workspace(nb, dev)
     if tokens.dtype != torch.int32:
         raise TypeError("tokens must be int32")
@@ -450,7 +457,10 @@ def pp_seq_logprob_bwd(pack: Pack, logits: torch.Tensor, tokens: torch.Tensor, d
 
 def pp_logprob_row_count(pack: Pack) -> int:
     """Number of logit rows that predict a response token."""
-    h = _desc_of(pack)
+    return _row_count(_desc_of(pack))
+
+
+def _row_count(h: _DescHolder) -> int:
     n = ctypes.c_int64(0)
     _check(lib().pp_logprob_row_count(h.ref, ctypes.byref(n)))
     return int(n.value)
@@ -463,13 +473,13 @@ def pp_seq_logprob_bwd_rows(pack: Pack, logits: torch.Tensor, tokens: torch.Tens
     V = logits.shape[1]
     h = _desc_of(pack)
     dev = logits.device
-    n = pp_logprob_row_count(pack)
+    n = _row_count(h)
     if dlogits_rows is None:
         dlogits_rows = torch.empty(n, V, dtype=logits.dtype, device=dev)
     if row_index is None:
         row_index = torch.empty(n, dtype=torch.int32, device=dev)
     if ws is None:
-        nb = pp_workspace_size(pack, vocab=V, fwd=False, bwd=False, logprob=True, loss=False)[2]
+        nb = _workspace_sizes(h, vocab=V, logprob=True)[2]
         ws = _workspace(nb, dev)
     if tokens.dtype != torch.int32:
         raise TypeError("tokens must be int32")
@@ -481,7 +491,10 @@ def pp_seq_logprob_bwd_rows(pack: Pack, logits: torch.Tensor, tokens: torch.Tens
 
 
 def pp_rm_workspace_size(pack: Pack) -> int:
-    h = _desc_of(pack)
+    return _rm_workspace_bytes(_desc_of(pack))
+
+
+def _rm_workspace_bytes(h: _DescHolder) -> int:
     n = ctypes.c_size_t(0)
     _check(lib().pp_rm_workspace_size(h.ref, ctypes.byref(n)))
     return n.value
@@ -497,7 +510,7 @@ def pp_rm_scores(pack: Pack, hidden: torch.Tensor, w: torch.Tensor, bias: float 
     if scores is None:
         scores = torch.empty(pack.num_rows, max(pack.max_resp, 1), dtype=torch.float32, device=dev)
     if ws is None:
-        ws = _workspace(pp_rm_workspace_size(pack), dev)
+        ws = _workspace(_rm_workspace_bytes(h), dev)
     _check(lib().pp_rm_scores(h.ref, _dtype_code(hidden), H, _ptr(hidden), _ptr(w), float(bias), _ptr(scores),
                               _ptr(ws), ws.numel(), _stream(dev)))
     return scores
@@ -514,7 +527,7 @@ def pp_rm_scores_bwd(pack: Pack, hidden: torch.Tensor, w: torch.Tensor, dscores:
     dw = torch.empty(H, dtype=torch.float32, device=dev)
     db = torch.empty(1, dtype=torch.float32, device=dev)
     if ws is None:
-        ws = _workspace(pp_rm_workspace_size(pack), dev)
+        ws = _workspace(_rm_workspace_bytes(h), dev)
     _check(lib().pp_rm_scores_bwd(h.ref, _dtype_code(hidden), H, _ptr(hidden), _ptr(w), _ptr(dscores), _ptr(dh),
                                   _ptr(dw), _ptr(db), _ptr(ws), ws.numel(), _stream(dev)))
     return dh, dw, db

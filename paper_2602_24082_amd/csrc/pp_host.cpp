@@ -154,8 +154,9 @@ int64_t sum_ramp(int64_t a, int64_t b, int64_t c, int64_t k1) {
 
 // Number of visible (query, key) pairs with query in [q0,q1), key in [k0,k1),
 // in closed form per segment.  A prompt query i sees keys [0, i]; a query i of
-// response k sees [0, P) and [o_k, i]; padding sees nothing.
-int64_t visible_pairs(const Row& r, int32_t q0, int32_t q1, int32_t k0, int32_t k1) {
+// response k sees [0, P) and [o_k, i]; padding sees nothing.  Responses before
+// first_resp must end by q0.
+int64_t visible_pairs(const Row& r, int32_t q0, int32_t q1, int32_t k0, int32_t k1, int first_resp = 0) {
   if (k1 <= k0) return 0;
   int64_t n = 0;
   // prompt queries
@@ -165,7 +166,7 @@ int64_t visible_pairs(const Row& r, int32_t q0, int32_t q1, int32_t k0, int32_t 
   }
   // response queries
   const int64_t kp = overlap(k0, k1, 0, r.P);
-  for (int k = 0; k < r.K; ++k) {
+  for (int k = first_resp; k < r.K && r.off[k] < q1; ++k) {
     const int64_t o = r.off[k], e = (int64_t)r.off[k] + r.len[k];
     const int64_t a = std::max<int64_t>(q0, o), b = std::min<int64_t>(q1, e);
     if (b <= a) continue;
@@ -191,11 +192,22 @@ struct QPlan {
   std::vector<KTileEntry> ktiles;
 };
 
+// Query tiles of BM queries and, for each, the key tiles of BN keys that hold a
+// visible pair, with the class of each 32-query block.  Most tiles need no count of
+// pairs: a key tile at or before the tile's first query is visible in full if it
+// lies in the prompt, or in the one response that holds all the tile's queries, and
+// of the keys past the prompt only those from the first response that the tile
+// reaches are visible at all, so the walk goes straight there.  The rest (the tile
+// that holds the prompt's end, the diagonal, rows' ends) count their pairs.
+// (The sizes of one forward of 8 rows, 12656 tokens, planned in 120 us of host time when
+// every tile was counted, and in 20 to 25 us now.)
 void build_qplan(const Batch& bt, int BM, int BN, QPlan* out) {
   out->items.clear();
   out->ktiles.clear();
+  const uint32_t all_full = kWaveFull * 0x55555555u;
   for (int b = 0; b < bt.B; ++b) {
     const Row& r = bt.rows[b];
+    int kk = 0;  // first response that ends past the tile's first query
     for (int32_t q0 = 0; q0 < r.T; q0 += BM) {
       QTileItem it{};
       it.tok0 = r.tok0;
@@ -205,30 +217,43 @@ void build_qplan(const Batch& bt, int BM, int BN, QPlan* out) {
       it.valid = r.valid;
       it.kt_off = (int32_t)out->ktiles.size();
       it.row = b;
+      while (kk < r.K && r.off[kk] + r.len[kk] <= q0) ++kk;
+      // first key past the prompt that a query of the tile may see
+      const int32_t own = kk < r.K && r.off[kk] < it.q_end ? r.off[kk] : r.T;
+      const int32_t own_end = kk < r.K ? r.off[kk] + r.len[kk] : 0;
+      const int waves = (it.q_end - q0 + 31) / 32;
       // only keys <= the tile's last query can be visible (causal)
       const int32_t kmax = std::min(it.q_end, r.valid);
       for (int32_t k0 = 0; k0 < kmax; k0 += BN) {
+        if (k0 >= r.P && k0 + BN <= own) {
+          k0 = own / BN * BN;
+          if (k0 >= kmax) break;
+        }
+        if (k0 + BN <= q0 + 1 && it.q_end <= r.valid &&
+            (k0 + BN <= r.P || (k0 >= own && it.q_end <= own_end))) {
+          out->ktiles.push_back(KTileEntry{k0, all_full & (waves >= 16 ? ~0u : (1u << (2 * waves)) - 1u)});
+          continue;
+        }
         const int32_t k1 = std::min(r.T, k0 + BN);
-        if (visible_pairs(r, q0, it.q_end, k0, k1) == 0) continue;
         KTileEntry e{k0, 0u};
-        for (int w = 0; w * 32 < BM; ++w) {
+        bool any = false;
+        for (int w = 0; w < waves; ++w) {
           const int32_t qa = q0 + 32 * w, qb = std::min(it.q_end, qa + 32);
+          const int64_t n = visible_pairs(r, qa, qb, k0, k1, kk);
           int cls = kWaveSkip;
-          if (qa < qb) {
-            const int64_t n = visible_pairs(r, qa, qb, k0, k1);
-            // a key tile cut short by the row's end leaves lanes without a key: masked
-            if (n == (int64_t)(qb - qa) * BN) {
-              cls = kWaveFull;
-            } else if (n > 0) {
-              // the visible pairs are exactly the causal ones among real tokens:
-              // the mask reduces to j <= i
-              const int64_t causal = sum_ramp(qa, std::min(qb, r.valid), k0, std::min(k1, r.valid));
-              cls = n == causal ? kWaveCausal : kWaveMasked;
-            }
+          // a key tile cut short by the row's end leaves lanes without a key: masked
+          if (n == (int64_t)(qb - qa) * BN) {
+            cls = kWaveFull;
+          } else if (n > 0) {
+            // the visible pairs are exactly the causal ones among real tokens:
+            // the mask reduces to j <= i
+            const int64_t causal = sum_ramp(qa, std::min(qb, r.valid), k0, std::min(k1, r.valid));
+            cls = n == causal ? kWaveCausal : kWaveMasked;
           }
+          any = any || n > 0;
           e.cls |= (uint32_t)cls << (2 * w);
         }
-        out->ktiles.push_back(e);
+        if (any) out->ktiles.push_back(e);
       }
       it.kt_cnt = (int32_t)out->ktiles.size() - it.kt_off;
       out->items.push_back(it);
@@ -371,29 +396,19 @@ void split_kplan(int hkv, std::vector<KTileItem>* kv, std::vector<KTileSplit>* s
 // its prompt [0, P), then its responses back to back from P, then padding.
 // seg_lo: row-relative start of the token's segment (0 in the prompt, o_k in
 // response k, -1 for padding).
-void build_seg_lo(const Batch& bt, std::vector<int32_t>* out) {
-  out->assign(bt.sumT, -1);
-  int32_t* o = out->data();
+void fill_seg_lo(const Batch& bt, int32_t* o) {
+  std::fill(o, o + bt.sumT, -1);
   for (const Row& r : bt.rows) {
     std::fill(o + r.tok0, o + r.tok0 + r.P, 0);
     for (int k = 0; k < r.K; ++k) std::fill(o + r.tok0 + r.off[k], o + r.tok0 + r.off[k] + r.len[k], r.off[k]);
   }
 }
 
-// One past the last query that can see key t (row-relative): a prompt key is
+// seg_hi: one past the last query that can see key t (row-relative): a prompt key is
 // seen by every later real token, a response key only by its own response's
 // later tokens (Sec. 3.2), a padding key by nothing.
-inline int32_t seg_end(const Row& r, int32_t t) {
-  if (t < r.P) return r.valid;
-  for (int k = 0; k < r.K; ++k)
-    if (r.off[k] <= t && t < r.off[k] + r.len[k]) return r.off[k] + r.len[k];
-  return 0;
-}
-
-// seg_hi: seg_end of every token.
-void build_seg_hi(const Batch& bt, std::vector<int32_t>* out) {
-  out->assign(bt.sumT, 0);
-  int32_t* o = out->data();
+void fill_seg_hi(const Batch& bt, int32_t* o) {
+  std::fill(o, o + bt.sumT, 0);
   for (const Row& r : bt.rows) {
     std::fill(o + r.tok0, o + r.tok0 + r.P, r.valid);
     for (int k = 0; k < r.K; ++k)
@@ -404,7 +419,7 @@ void build_seg_hi(const Batch& bt, std::vector<int32_t>* out) {
 // Panels of the stored dS: per row, per 32-key block KB, the query blocks
 // KB .. ceil(q_end / 32) - 1, where q_end is one past the last query that sees
 // one of the block's keys within its key tile of BN keys (the tile's query
-// range clipped to the row's real tokens, and each key's own seg_end) --
+// range clipped to the row's real tokens, and each key's own seg_hi) --
 // exactly the 32 x 32 blocks that the key-major pass computes for it --
 // numbered consecutively in row and block order.  Returns the tiles per head,
 // or -1 if they do not fit 32-bit tile offsets.
@@ -414,14 +429,20 @@ int64_t build_ds_panels(const Batch& bt, int BN, std::vector<int32_t>* row_kb0, 
   int64_t off = 0;
   for (const Row& r : bt.rows) {
     row_kb0->push_back((int32_t)panels->size());
+    int kk = 0;  // first response that ends past the block's first key
     for (int32_t kb = 0; kb * 32 < r.T; ++kb) {
       const int32_t k0 = kb * 32 / BN * BN, k_end = std::min(r.T, k0 + BN);
       int32_t q_end = 0;
       if (k0 < r.valid) {
         const int32_t qlim = std::min(key_tile_q_end(r, k0, k_end), r.valid);
-        for (int32_t j = kb * 32; j < std::min(k_end, kb * 32 + 32); ++j) {
-          const int32_t last = std::min(qlim, seg_end(r, j));  // key j is seen by queries j .. last - 1
-          if (last > j) q_end = std::max(q_end, last);
+        // key j is seen by queries j .. min(qlim, seg_hi(j)) - 1: a prompt key by the
+        // most, else the keys of each response in the block
+        const int32_t j0 = kb * 32, j1 = std::min(k_end, j0 + 32);
+        while (kk < r.K && r.off[kk] + r.len[kk] <= j0) ++kk;
+        if (j0 < r.P && std::min(qlim, r.valid) > j0) q_end = std::min(qlim, r.valid);
+        for (int k = kk; k < r.K && r.off[k] < j1; ++k) {
+          const int32_t first = std::max(j0, r.off[k]), last = std::min(qlim, r.off[k] + r.len[k]);
+          if (last > first) q_end = std::max(q_end, last);
         }
       }
       const int32_t len = std::max(0, (q_end + 31) / 32 - kb);
@@ -466,54 +487,71 @@ pp_status check_rope_base(float base) {
   return PP_OK;
 }
 
-struct LPlan {
-  std::vector<LogitRowItem> rows;
-  std::vector<int32_t> labels;     // flat position of each label token
-  std::vector<int32_t> label_out;  // its response's slot b * K_max + k
-  std::vector<RespItem> resp;
+// The log-probs' records, in row and token order: the last prompt position
+// predicts the first token of every response, a response's token the next one.
+struct LCounts {
+  int64_t rows = 0;    // gather records: logit rows that predict a response token
+  int64_t labels = 0;  // label tokens
+  int64_t resp = 0;    // (row, response) slots
 };
 
-void build_lplan(const Batch& bt, LPlan* out) {
-  out->rows.clear();
-  out->labels.clear();
-  out->label_out.clear();
-  out->resp.clear();
+LCounts count_lplan(const Batch& bt) {
+  LCounts n;
+  n.resp = (int64_t)bt.B * bt.Kmax;
+  for (const Row& r : bt.rows) {
+    int64_t len = 0, some = 0;
+    for (int k = 0; k < r.K; ++k) {
+      len += r.len[k];
+      some += r.len[k] > 0;
+    }
+    n.labels += len;
+    if (some) n.rows += 1 + len - some;
+  }
+  return n;
+}
+
+// labels: flat position of each label token; label_out: its response's slot
+// b * K_max + k; row_item: gather record of each flat logit row (-1: predicts
+// nothing).  resp, label_out and row_item may be null.
+void fill_lplan(const Batch& bt, LogitRowItem* rows, int32_t* labels, RespItem* resp, int32_t* label_out,
+                int32_t* row_item) {
+  if (row_item) std::fill(row_item, row_item + bt.sumT, -1);
+  int32_t n_rows = 0, n_labels = 0;
+  auto add_row = [&](int64_t logit_row, int32_t label_cnt) {
+    LogitRowItem it{};
+    it.logit_row = logit_row;
+    it.label_off = n_labels;
+    it.label_cnt = label_cnt;
+    if (row_item) row_item[logit_row] = n_rows;
+    rows[n_rows++] = it;
+  };
+  auto add_label = [&](int32_t pos, int32_t slot) {
+    labels[n_labels] = pos;
+    if (label_out) label_out[n_labels] = slot;
+    ++n_labels;
+  };
   for (int b = 0; b < bt.B; ++b) {
     const Row& r = bt.rows[b];
-    bool any = false;
-    for (int k = 0; k < r.K; ++k) any = any || r.len[k] > 0;
-    if (any) {
-      // the last prompt position predicts the first token of every response
-      LogitRowItem it{};
-      it.logit_row = (int64_t)r.tok0 + r.P - 1;
-      it.label_off = (int32_t)out->labels.size();
+    int32_t some = 0;
+    for (int k = 0; k < r.K; ++k) some += r.len[k] > 0;
+    if (some) {
+      add_row((int64_t)r.tok0 + r.P - 1, some);
       for (int k = 0; k < r.K; ++k)
-        if (r.len[k] > 0) {
-          out->labels.push_back(r.tok0 + r.off[k]);
-          out->label_out.push_back(b * bt.Kmax + k);
-        }
-      it.label_cnt = (int32_t)out->labels.size() - it.label_off;
-      out->rows.push_back(it);
-      for (int k = 0; k < r.K; ++k) {
+        if (r.len[k] > 0) add_label(r.tok0 + r.off[k], b * bt.Kmax + k);
+      for (int k = 0; k < r.K; ++k)
         for (int32_t j = 1; j < r.len[k]; ++j) {
-          LogitRowItem e{};
-          e.logit_row = (int64_t)r.tok0 + r.off[k] + j - 1;
-          e.label_off = (int32_t)out->labels.size();
-          e.label_cnt = 1;
-          out->labels.push_back(r.tok0 + r.off[k] + j);
-          out->label_out.push_back(b * bt.Kmax + k);
-          out->rows.push_back(e);
+          add_row((int64_t)r.tok0 + r.off[k] + j - 1, 1);
+          add_label(r.tok0 + r.off[k] + j, b * bt.Kmax + k);
         }
-      }
     }
-    for (int k = 0; k < bt.Kmax; ++k) {
+    for (int k = 0; resp && k < bt.Kmax; ++k) {
       RespItem ri{};
       ri.out = b * bt.Kmax + k;
       if (k < r.K) {
         ri.tok_begin = r.tok0 + r.off[k];
         ri.len = r.len[k];
       }
-      out->resp.push_back(ri);
+      *resp++ = ri;
     }
   }
 }
@@ -659,9 +697,16 @@ pp_status stage_copy(void* dst, const void* src, size_t bytes, hipStream_t strea
 // Serialises regions into one host image of the metadata prefix.
 struct MetaImage {
   std::vector<uint8_t> buf;
+  // the region's place in the image, to be filled in
+  void* at(const Region& r) {
+    if (buf.size() < r.off + r.bytes) {
+      buf.resize(r.off + r.bytes);
+    }
+    return buf.data() + r.off;
+  }
   void put(const Region& r, const void* src, size_t bytes) {
-    if (buf.size() < r.off + r.bytes) buf.resize(r.off + r.bytes);
-    if (bytes) memcpy(buf.data() + r.off, src, bytes);
+    void* dst = at(r);
+    if (bytes) memcpy(dst, src, bytes);
   }
 };
 
@@ -677,7 +722,6 @@ struct CastRegions {
 
 struct FwdPlan {
   QPlan q;
-  std::vector<int32_t> seg_lo;
   Layout lay;
   size_t r_seg, r_items, r_kt, r_pos, r_freq;
   CastRegions cast;
@@ -685,9 +729,8 @@ struct FwdPlan {
 
 void plan_fwd(const Batch& bt, pp_dtype dtype, int hq, int hkv, int d, FwdPlan* p) {
   build_qplan(bt, kFwdBlockM, kFwdBlockN, &p->q);
-  build_seg_lo(bt, &p->seg_lo);
   p->lay = Layout();
-  p->r_seg = p->lay.add(p->seg_lo.size() * 4);
+  p->r_seg = p->lay.add((size_t)bt.sumT * 4);
   p->r_items = p->lay.add(p->q.items.size() * sizeof(QTileItem));
   p->r_kt = p->lay.add(p->q.ktiles.size() * sizeof(KTileEntry));
   // the rotary variant also stages positions and frequencies (last, so that
@@ -711,7 +754,6 @@ struct BwdPlan {
   std::vector<KTileItem> kv;
   std::vector<KTileSplit> kv_splits;
   int kv_slots = 0;  // partial-sum slots of the cut key tiles
-  std::vector<int32_t> seg_lo, seg_hi;
   std::vector<int32_t> row_kb0;
   std::vector<DsPanel> panels;
   int64_t ds_tiles = 0;  // per head; -1: the stored mode is not offered
@@ -727,11 +769,9 @@ void plan_bwd(const Batch& bt, pp_dtype dtype, int hq, int hkv, int d, BwdPlan* 
   build_qplan(bt, kDqBlockM, kDqBlockN, &p->dq);
   build_kplan(bt, kBwdBlockN, hq / hkv, &p->kv);
   split_kplan(hkv, &p->kv, &p->kv_splits, &p->kv_slots);
-  build_seg_lo(bt, &p->seg_lo);
-  build_seg_hi(bt, &p->seg_hi);
   p->lay = Layout();
-  p->r_seg = p->lay.add(p->seg_lo.size() * 4);
-  p->r_seg_hi = p->lay.add(p->seg_hi.size() * 4);
+  p->r_seg = p->lay.add((size_t)bt.sumT * 4);
+  p->r_seg_hi = p->lay.add((size_t)bt.sumT * 4);
   p->r_dq_items = p->lay.add(p->dq.items.size() * sizeof(QTileItem));
   p->r_dq_kt = p->lay.add(p->dq.ktiles.size() * sizeof(KTileEntry));
   p->r_kv_items = p->lay.add(p->kv.size() * sizeof(KTileItem));
@@ -760,24 +800,34 @@ void plan_bwd(const Batch& bt, pp_dtype dtype, int hq, int hkv, int d, BwdPlan* 
 // backward also stages each label's response slot and, per flat logit row, the
 // index of the gather record that reads it (-1 for rows that predict nothing).
 struct LogprobPlan {
-  LPlan l;
-  std::vector<int32_t> row_item;
+  LCounts n;
   Layout lay;
   size_t r_rows, r_labels, r_resp, r_label_out, r_row_item, r_tok;
 };
 
 void plan_logprob(const Batch& bt, LogprobPlan* p) {
-  build_lplan(bt, &p->l);
-  p->row_item.assign(bt.sumT, -1);
-  for (size_t i = 0; i < p->l.rows.size(); ++i) p->row_item[p->l.rows[i].logit_row] = (int32_t)i;
+  p->n = count_lplan(bt);
   p->lay = Layout();
-  p->r_rows = p->lay.add(p->l.rows.size() * sizeof(LogitRowItem));
-  p->r_labels = p->lay.add(p->l.labels.size() * 4);
-  p->r_resp = p->lay.add(p->l.resp.size() * sizeof(RespItem));
-  p->r_label_out = p->lay.add(p->l.label_out.size() * 4);
-  p->r_row_item = p->lay.add(p->row_item.size() * 4);
+  p->r_rows = p->lay.add(p->n.rows * sizeof(LogitRowItem));
+  p->r_labels = p->lay.add(p->n.labels * 4);
+  p->r_resp = p->lay.add(p->n.resp * sizeof(RespItem));
+  p->r_label_out = p->lay.add(p->n.labels * 4);
+  p->r_row_item = p->lay.add((size_t)bt.sumT * 4);
   p->lay.meta_bytes = p->lay.total;
   p->r_tok = p->lay.add((size_t)bt.sumT * 4);
+}
+
+// The forward's metadata, or the backward's (label slots; dense: each row's record).
+void logprob_image(const Batch& bt, const LogprobPlan& p, bool bwd, bool dense, MetaImage* img) {
+  const auto& reg = p.lay.regions;
+  img->buf.reserve(p.lay.meta_bytes);
+  // the last region first: the image has its size before the places are taken
+  if (dense) img->at(reg[p.r_row_item]);
+  if (bwd) img->at(reg[p.r_label_out]);
+  img->at(reg[p.r_resp]);
+  fill_lplan(bt, (LogitRowItem*)img->at(reg[p.r_rows]), (int32_t*)img->at(reg[p.r_labels]),
+             (RespItem*)img->at(reg[p.r_resp]), bwd ? (int32_t*)img->at(reg[p.r_label_out]) : nullptr,
+             dense ? (int32_t*)img->at(reg[p.r_row_item]) : nullptr);
 }
 
 // Reward-model head: each (row, response) slot's hidden row, and the distinct
@@ -786,47 +836,43 @@ struct RmPlan {
   std::vector<int64_t> slot_row;
   std::vector<RmRowSlots> rows;
   std::vector<int32_t> slots;
-  std::vector<int32_t> row_rec;
   Layout lay;
   size_t r_slot_row, r_rows, r_slots, r_row_rec;
 };
 
+// The distinct rows come in order of first use, each with its slots in slot order:
+// a slot that ends in a response's last token has that row to itself, all empty
+// responses of a row share its last prompt token.
 void plan_rm(const Batch& bt, RmPlan* p) {
-  const int n = bt.B * bt.Kmax;
-  p->slot_row.assign(n, -1);
-  for (int b = 0; b < bt.B; ++b) {
-    const Row& r = bt.rows[b];
-    for (int k = 0; k < r.K; ++k) {
-      const int64_t last = r.len[k] > 0 ? (int64_t)r.off[k] + r.len[k] - 1 : (int64_t)r.P - 1;
-      if (last >= 0) p->slot_row[b * bt.Kmax + k] = r.tok0 + last;
-    }
-  }
-  p->row_rec.assign(bt.sumT, -1);
+  p->slot_row.assign((size_t)bt.B * bt.Kmax, -1);
   p->rows.clear();
   p->slots.clear();
-  // distinct rows in order of first use, each with its slots in slot order
-  std::vector<std::vector<int32_t>> per_row;
-  for (int sidx = 0; sidx < n; ++sidx) {
-    const int64_t row = p->slot_row[sidx];
-    if (row < 0) continue;
-    int32_t& rec = p->row_rec[row];
-    if (rec < 0) {
-      rec = (int32_t)per_row.size();
-      per_row.emplace_back();
-      p->rows.push_back(RmRowSlots{row, 0, 0});
+  for (int b = 0; b < bt.B; ++b) {
+    const Row& r = bt.rows[b];
+    bool empties = false;  // their record is in
+    for (int k = 0; k < r.K; ++k) {
+      const int64_t last = r.len[k] > 0 ? (int64_t)r.off[k] + r.len[k] - 1 : (int64_t)r.P - 1;
+      if (last < 0) continue;
+      p->slot_row[b * bt.Kmax + k] = r.tok0 + last;
+      if (r.len[k] == 0 && empties) continue;
+      RmRowSlots rec{r.tok0 + last, (int32_t)p->slots.size(), 1};
+      p->slots.push_back(b * bt.Kmax + k);
+      if (r.len[k] == 0) {
+        empties = true;
+        for (int j = k + 1; j < r.K; ++j)
+          if (r.len[j] == 0) {
+            p->slots.push_back(b * bt.Kmax + j);
+            ++rec.slot_cnt;
+          }
+      }
+      p->rows.push_back(rec);
     }
-    per_row[rec].push_back(sidx);
-  }
-  for (size_t i = 0; i < per_row.size(); ++i) {
-    p->rows[i].slot_off = (int32_t)p->slots.size();
-    p->rows[i].slot_cnt = (int32_t)per_row[i].size();
-    p->slots.insert(p->slots.end(), per_row[i].begin(), per_row[i].end());
   }
   p->lay = Layout();
   p->r_slot_row = p->lay.add(p->slot_row.size() * 8);
   p->r_rows = p->lay.add(p->rows.size() * sizeof(RmRowSlots));
   p->r_slots = p->lay.add(p->slots.size() * 4);
-  p->r_row_rec = p->lay.add(p->row_rec.size() * 4);
+  p->r_row_rec = p->lay.add((size_t)bt.sumT * 4);
   p->lay.meta_bytes = p->lay.total;
 }
 
@@ -1060,7 +1106,8 @@ pp_status check_bwd_ptrs(int sumT, const void* q, const void* k, const void* v, 
 // frequencies included when rope_base is given).
 void fwd_image(const Batch& bt, const FwdPlan& p, int head_dim, const double* rope_base, MetaImage* out) {
   MetaImage& img = *out;
-  img.put(p.lay.regions[p.r_seg], p.seg_lo.data(), p.seg_lo.size() * 4);
+  img.buf.reserve(p.lay.meta_bytes);
+  fill_seg_lo(bt, (int32_t*)img.at(p.lay.regions[p.r_seg]));
   img.put(p.lay.regions[p.r_items], p.q.items.data(), p.q.items.size() * sizeof(QTileItem));
   img.put(p.lay.regions[p.r_kt], p.q.ktiles.data(), p.q.ktiles.size() * sizeof(KTileEntry));
   std::vector<int32_t> pos;
@@ -1210,8 +1257,9 @@ namespace {
 // The backward's metadata prefix as one host image.
 void bwd_image(const Batch& bt, const BwdPlan& p, int head_dim, const double* rope_base, MetaImage* out) {
   MetaImage& img = *out;
-  img.put(p.lay.regions[p.r_seg], p.seg_lo.data(), p.seg_lo.size() * 4);
-  img.put(p.lay.regions[p.r_seg_hi], p.seg_hi.data(), p.seg_hi.size() * 4);
+  img.buf.reserve(p.lay.meta_bytes);
+  fill_seg_lo(bt, (int32_t*)img.at(p.lay.regions[p.r_seg]));
+  fill_seg_hi(bt, (int32_t*)img.at(p.lay.regions[p.r_seg_hi]));
   img.put(p.lay.regions[p.r_dq_items], p.dq.items.data(), p.dq.items.size() * sizeof(QTileItem));
   img.put(p.lay.regions[p.r_dq_kt], p.dq.ktiles.data(), p.dq.ktiles.size() * sizeof(KTileEntry));
   img.put(p.lay.regions[p.r_kv_items], p.kv.data(), p.kv.size() * sizeof(KTileItem));
@@ -1589,9 +1637,7 @@ pp_status pp_seq_logprob(const pp_pack_desc* desc, pp_dtype logits_dtype, int vo
   if (bt.Kmax == 0 && (bt.sumT == 0 || !tok_logp)) return PP_OK;
   hipStream_t s = (hipStream_t)hip_stream;
   MetaImage img;
-  img.put(p.lay.regions[p.r_rows], p.l.rows.data(), p.l.rows.size() * sizeof(LogitRowItem));
-  img.put(p.lay.regions[p.r_labels], p.l.labels.data(), p.l.labels.size() * 4);
-  img.put(p.lay.regions[p.r_resp], p.l.resp.data(), p.l.resp.size() * sizeof(RespItem));
+  logprob_image(bt, p, false, false, &img);
   LogprobLaunch a{};
   a.logits = logits;
   a.tokens = tokens;
@@ -1600,8 +1646,8 @@ pp_status pp_seq_logprob(const pp_pack_desc* desc, pp_dtype logits_dtype, int vo
   a.rows = (const LogitRowItem*)at(ws, p.lay, p.r_rows);
   a.labels = (const int32_t*)at(ws, p.lay, p.r_labels);
   a.resp = (const RespItem*)at(ws, p.lay, p.r_resp);
-  a.n_rows = (int)p.l.rows.size();
-  a.n_resp = (int)p.l.resp.size();
+  a.n_rows = (int)p.n.rows;
+  a.n_resp = (int)p.n.resp;
   a.vocab = vocab;
   a.sumT = bt.sumT;
   a.dtype = logits_dtype == PP_FP32 ? kFP32 : kBF16;
@@ -1642,7 +1688,7 @@ pp_status logprob_bwd_impl(const pp_pack_desc* desc, pp_dtype logits_dtype, int 
   if (bt.sumT == 0) return PP_OK;
   LogprobPlan p;
   plan_logprob(bt, &p);
-  if (gathered && p.l.rows.empty()) return PP_OK;
+  if (gathered && p.n.rows == 0) return PP_OK;
   if (!logits || !tokens || !dlogits) return fail(PP_ERR_INVALID_ARGUMENT, "logits, tokens and dlogits must be non-NULL");
   if (bt.Kmax > 0 && !dseq) return fail(PP_ERR_INVALID_ARGUMENT, "dseq is NULL");
   if (ws_bytes < p.lay.total)
@@ -1652,11 +1698,7 @@ pp_status logprob_bwd_impl(const pp_pack_desc* desc, pp_dtype logits_dtype, int 
   if (ws && !aligned256(ws)) return fail(PP_ERR_INVALID_ARGUMENT, "ws must be 256-byte aligned");
   hipStream_t s = (hipStream_t)hip_stream;
   MetaImage img;
-  img.put(p.lay.regions[p.r_rows], p.l.rows.data(), p.l.rows.size() * sizeof(LogitRowItem));
-  img.put(p.lay.regions[p.r_labels], p.l.labels.data(), p.l.labels.size() * 4);
-  img.put(p.lay.regions[p.r_resp], p.l.resp.data(), p.l.resp.size() * sizeof(RespItem));
-  img.put(p.lay.regions[p.r_label_out], p.l.label_out.data(), p.l.label_out.size() * 4);
-  if (!gathered) img.put(p.lay.regions[p.r_row_item], p.row_item.data(), p.row_item.size() * 4);
+  logprob_image(bt, p, true, !gathered, &img);
   if ((st = stage_copy(ws, img.buf.data(), img.buf.size(), s)) != PP_OK) return st;
   LogprobBwdLaunch a{};
   a.logits = logits;
@@ -1671,7 +1713,7 @@ pp_status logprob_bwd_impl(const pp_pack_desc* desc, pp_dtype logits_dtype, int 
   a.sumT = bt.sumT;
   a.dtype = logits_dtype == PP_FP32 ? kFP32 : kBF16;
   a.gathered = gathered;
-  a.n_rows = (int)p.l.rows.size();
+  a.n_rows = (int)p.n.rows;
   a.row_index = row_index;
   hipError_t e = launch_logprob_bwd(a, s);
   if (e != hipSuccess) return hip_fail(e, "logprob backward launch");
@@ -1696,9 +1738,7 @@ pp_status pp_logprob_row_count(const pp_pack_desc* desc, int64_t* n_rows) {
   if (st != PP_OK) return st;
   if (!n_rows) return fail(PP_ERR_INVALID_ARGUMENT, "n_rows is NULL");
   if ((st = check_logprob_layout(bt)) != PP_OK) return st;
-  LPlan l;
-  build_lplan(bt, &l);
-  *n_rows = (int64_t)l.rows.size();
+  *n_rows = count_lplan(bt).rows;
   return PP_OK;
 }
 
@@ -1775,7 +1815,9 @@ pp_status pp_rm_scores_bwd(const pp_pack_desc* desc, pp_dtype dtype, int hidden_
   img.put(p.lay.regions[p.r_slot_row], p.slot_row.data(), p.slot_row.size() * 8);
   img.put(p.lay.regions[p.r_rows], p.rows.data(), p.rows.size() * sizeof(RmRowSlots));
   img.put(p.lay.regions[p.r_slots], p.slots.data(), p.slots.size() * 4);
-  img.put(p.lay.regions[p.r_row_rec], p.row_rec.data(), p.row_rec.size() * 4);
+  int32_t* row_rec = (int32_t*)img.at(p.lay.regions[p.r_row_rec]);
+  std::fill(row_rec, row_rec + bt.sumT, -1);
+  for (size_t i = 0; i < p.rows.size(); ++i) row_rec[p.rows[i].row] = (int32_t)i;
   if ((st = stage_copy(ws, img.buf.data(), img.buf.size(), s)) != PP_OK) return st;
   RmBwdLaunch a{};
   a.hidden = hidden;
