@@ -12,7 +12,7 @@
 //   logprob_bwd    one workgroup per flat logit row: the gradient of the
 //                  weighted response sums, -c softmax + label terms, zeros for
 //                  rows that predict nothing (HBM-bound: one read of the needed
-//                  rows, a cached re-read, one write of every row)
+//                  rows, one write of every row)
 //   segsum         one wave per (row, response) slot: fixed-order sum of the
 //                  response's token log-probs -> seq[b, k]
 //   pair_loss      one workgroup: z = beta (pol - ref), softplus over ranked
@@ -110,26 +110,17 @@ struct RowSplit {
   __device__ __forceinline__ int extra(int tid) const { return tid < head ? tid : tid + nvec * N; }
 };
 
-// ln sum_v exp(x[v]) of one logit row, for every thread of a kLpThreads
-// workgroup: one streaming pass of aligned 16-byte loads (kLpUnroll in flight per
-// thread) keeping an online (max, sum) per thread, the row's head and tail
-// elements last, then a fixed-order workgroup combine.  HBM bound.  Rows that
-// start on no 16-byte boundary used to be read element by element: 2224 rows of
-// 50257 fp32 took 135 us and take 69 us (6.5 TB/s).
-template <typename T>
-__device__ float row_logsumexp(const T* __restrict__ x, int vocab) {
-  const int tid = threadIdx.x;
-  MaxSum acc = {kNegInf, 0.f};
+// Online (max, sum) over the vectors first, first + THREADS, ... below nvec of one
+// thread, kLpUnroll loads in flight.
+template <typename T, int THREADS>
+__device__ __forceinline__ MaxSum stream_max_sum(const u32x4* __restrict__ xv, int first, int nvec) {
   constexpr int N = Vec16<T>::N;
-  const RowSplit<T> rs(x, vocab);
-  const int nvec = rs.nvec;
-  const u32x4* xv = reinterpret_cast<const u32x4*>(x + rs.head);
-  const float xe = tid < rs.n_extra ? elem<T>(x, rs.extra(tid)) : kNegInf;
-  for (int base = 0; base < nvec; base += kLpThreads * kLpUnroll) {
+  MaxSum acc = {kNegInf, 0.f};
+  for (int base = first; base < nvec; base += THREADS * kLpUnroll) {
     u32x4 u[kLpUnroll];
 #pragma unroll
     for (int j = 0; j < kLpUnroll; ++j) {
-      const int vi = base + j * kLpThreads + tid;
+      const int vi = base + j * THREADS;
       u[j] = vi < nvec ? __builtin_nontemporal_load(xv + vi) : u32x4{0, 0, 0, 0};
     }
     float f[kLpUnroll * N];
@@ -138,8 +129,7 @@ __device__ float row_logsumexp(const T* __restrict__ x, int vocab) {
     float mloc = kNegInf;
 #pragma unroll
     for (int j = 0; j < kLpUnroll; ++j) {
-      const int vi = base + j * kLpThreads + tid;
-      if (vi < nvec) {
+      if (base + j * THREADS < nvec) {
 #pragma unroll
         for (int e = 0; e < N; ++e) mloc = fmaxf(mloc, f[j * N + e]);
       }
@@ -150,8 +140,7 @@ __device__ float row_logsumexp(const T* __restrict__ x, int vocab) {
       float s = acc.s * fast_exp2(acc.m * kLog2e - ml);
 #pragma unroll
       for (int j = 0; j < kLpUnroll; ++j) {
-        const int vi = base + j * kLpThreads + tid;
-        if (vi < nvec) {
+        if (base + j * THREADS < nvec) {
 #pragma unroll
           for (int e = 0; e < N; ++e) s += fast_exp2(fmaf(f[j * N + e], kLog2e, -ml));
         }
@@ -159,6 +148,21 @@ __device__ float row_logsumexp(const T* __restrict__ x, int vocab) {
       acc = {m, s};
     }
   }
+  return acc;
+}
+
+// ln sum_v exp(x[v]) of one logit row, for every thread of a kLpThreads
+// workgroup: one streaming pass of aligned 16-byte loads (kLpUnroll in flight per
+// thread) keeping an online (max, sum) per thread, the row's head and tail
+// elements last, then a fixed-order workgroup combine.  HBM bound.  Rows that
+// start on no 16-byte boundary used to be read element by element: 2224 rows of
+// 50257 fp32 took 135 us and take 69 us (6.5 TB/s).
+template <typename T>
+__device__ float row_logsumexp(const T* __restrict__ x, int vocab) {
+  const int tid = threadIdx.x;
+  const RowSplit<T> rs(x, vocab);
+  const float xe = tid < rs.n_extra ? elem<T>(x, rs.extra(tid)) : kNegInf;
+  MaxSum acc = stream_max_sum<T, kLpThreads>(reinterpret_cast<const u32x4*>(x + rs.head), tid, rs.nvec);
   if (tid < rs.n_extra) acc = combine(acc, MaxSum{xe, 1.f});
   // workgroup reduction of (m, s)
   for (int off = 32; off > 0; off >>= 1) {
@@ -228,108 +232,13 @@ struct __attribute__((packed, aligned(sizeof(T)))) Vec16Any {
 // g over the labels that row r predicts,
 //   dlogits[r, v] = -c softmax(x_r)[v] + sum_{labels y = v} g,
 // the gradient of sum_bk g_bk seq_bk; rows that predict nothing get 0 and a
-// label outside the vocabulary makes its row NaN.  The row's logsumexp is
-// recomputed with one pass; a second pass re-reads the row (mostly from the
-// caches) and streams the gradient out.
-template <typename T>
-__global__ __launch_bounds__(kLpThreads) void logprob_bwd_kernel(LogprobBwdLaunch a) {
-  const int tid = threadIdx.x;
-  const int vocab = a.vocab;
-  // dense: workgroup = flat logit row r, output row r; gathered: workgroup =
-  // gather record, output row = record index
-  const int64_t o_row = blockIdx.x;
-  const int item = a.gathered ? (int)blockIdx.x : a.row_item[blockIdx.x];
-  const int64_t r = a.gathered ? a.rows[item].logit_row : (int64_t)blockIdx.x;
-  if (a.gathered && a.row_index && tid == 0) a.row_index[item] = (int32_t)r;
-  T* out = reinterpret_cast<T*>(a.dlogits) + o_row * (int64_t)vocab;
-  constexpr int N = Vec16<T>::N;
-  // the output row's own 16-byte boundaries; the input row may lie on others
-  const RowSplit<T> rs(out, vocab);
-  const int nvec = rs.nvec;
-  u32x4* ov = reinterpret_cast<u32x4*>(out + rs.head);
-  if (item < 0) {
-    for (int vi = tid; vi < nvec; vi += kLpThreads) __builtin_nontemporal_store(u32x4{0, 0, 0, 0}, ov + vi);
-    if (tid < rs.n_extra) out[rs.extra(tid)] = (T)0.f;
-    return;
-  }
-  const LogitRowItem it = a.rows[item];
-  const T* x = reinterpret_cast<const T*>(a.logits) + r * (int64_t)vocab;
-  __shared__ int s_y[kMaxRowLabels];
-  __shared__ float s_g[kMaxRowLabels];
-  __shared__ float s_c;
-  __shared__ int s_bad;
-  const int cnt = it.label_cnt;
-  if (tid == 0) s_bad = 0;
-  __syncthreads();
-  for (int j = tid; j < cnt; j += kLpThreads) {
-    const int32_t y = a.tokens[a.labels[it.label_off + j]];
-    s_y[j] = y;
-    s_g[j] = a.dseq[a.label_out[it.label_off + j]];
-    if (y < 0 || y >= vocab) s_bad = 1;
-  }
-  const float lse = row_logsumexp<T>(x, vocab);  // its barriers publish s_y, s_g, s_bad
-  if (tid == 0) {
-    float c = 0.f;
-    for (int j = 0; j < cnt; ++j) c += s_g[j];
-    s_c = c;
-  }
-  __syncthreads();
-  const float c = s_c;
-  const bool bad = s_bad != 0;
-  const float lse2 = lse * kLog2e;
-  // -c softmax for every element; the few label terms are added only to the
-  // vectors that hold a label
-  auto label_terms = [&](float* f, int v0, int n) {
-    for (int j = 0; j < cnt; ++j) {
-      const int d = s_y[j] - v0;
-      if ((unsigned)d < (unsigned)n) {
-#pragma unroll
-        for (int e = 0; e < N; ++e) f[e] += (e == d) ? s_g[j] : 0.f;
-      }
-    }
-  };
-  const Vec16Any<T>* xv = reinterpret_cast<const Vec16Any<T>*>(x + rs.head);
-  const float xe = tid < rs.n_extra ? elem<T>(x, rs.extra(tid)) : 0.f;
-  for (int base = 0; base < nvec; base += kLpThreads * kLpUnroll) {
-    u32x4 u[kLpUnroll];
-#pragma unroll
-    for (int j = 0; j < kLpUnroll; ++j) {
-      const int vi = base + j * kLpThreads + tid;
-      u[j] = vi < nvec ? xv[vi].v : u32x4{0, 0, 0, 0};
-    }
-#pragma unroll
-    for (int j = 0; j < kLpUnroll; ++j) {
-      const int vi = base + j * kLpThreads + tid;
-      if (vi < nvec) {
-        float f[N];
-        Vec16<T>::unpack(u[j], f);
-#pragma unroll
-        for (int e = 0; e < N; ++e) f[e] = -c * fast_exp2(fmaf(f[e], kLog2e, -lse2));
-        label_terms(f, rs.head + vi * N, N);
-        if (bad) {
-#pragma unroll
-          for (int e = 0; e < N; ++e) f[e] = __builtin_nanf("");
-        }
-        __builtin_nontemporal_store(Pack16<T>::pack(f), ov + vi);
-      }
-    }
-  }
-  if (tid < rs.n_extra) {
-    float f[N] = {};
-    f[0] = -c * fast_exp2(fmaf(xe, kLog2e, -lse2));
-    label_terms(f, rs.extra(tid), 1);
-    out[rs.extra(tid)] = (T)(bad ? __builtin_nanf("") : f[0]);
-  }
-}
-
-// Log-prob backward with the row held in registers: one workgroup per flat
-// logit row.  A needed row is read from HBM once -- thread t loads the 16-byte
-// vectors t, t + THREADS, ... (R of them at most) -- its logsumexp is formed from
-// the registers (thread maximum, then thread sum of exponentials, then a
-// fixed-order workgroup combine), and the gradient is computed from the same
-// registers and streamed out, so each row costs one read and one write of HBM
-// (the two-pass kernel above reads it twice).  Rows that predict nothing are
-// streamed zeros.
+// label outside the vocabulary makes its row NaN.
+//
+// The row is held in registers: thread t loads the 16-byte vectors t, t + THREADS,
+// ... (R of them), its logsumexp is formed from them (thread maximum, then thread
+// sum of exponentials, then a fixed-order workgroup combine), and the gradient is
+// computed from the same registers and streamed out, so each row costs one read and
+// one write of HBM.  Rows that predict nothing are streamed zeros.
 //
 // A workgroup first loads, then computes, then stores, so several of them per
 // compute unit are what keeps loads and stores in flight together, as far as the
@@ -343,20 +252,23 @@ __global__ __launch_bounds__(kLpThreads) void logprob_bwd_kernel(LogprobBwdLaunc
 // 3864 gathered rows of 32000 bf16 values take 92 us (155 us with the 1024 x 19
 // shape), 2224 of 50257 bf16 86 us.
 //
+// OVER: longer rows keep 1024 x 16 vectors and stream the rest twice, the second
+// time soon after the first and from the caches (2047 rows of 128256 fp32 values:
+// 588 us when all of the row was read twice, 474 us).
+//
 // EDGE: rows that start on no 16-byte boundary.  The vectors lie on the input
 // row's boundaries (so the logsumexp does not depend on where the output goes),
 // the stores where the output row has them, and one thread each takes the head
-// and tail elements; that costs registers (R 18 instead of 19).  The
-// two-pass kernel with element loads took 283 us on those 2224 rows, and 814 us
-// instead of 375 us on 2047 rows of 151999 bf16 values (now two passes of vectors).
+// and tail elements; that costs registers (R 18 instead of 19).  Element by element
+// those 2224 rows took 283 us.
 template <int R>
 __device__ __forceinline__ void opaque(u32x4 (&u)[R]) {
 #pragma unroll
   for (int j = 0; j < R; ++j) asm volatile("" : "+v"(u[j]));
 }
 
-template <typename T, int THREADS, int R, bool EDGE>
-__global__ __launch_bounds__(THREADS, R <= 8 ? 8 : 4) void logprob_bwd_reg_kernel(LogprobBwdLaunch a) {
+template <typename T, int THREADS, int R, bool EDGE, bool OVER>
+__global__ __launch_bounds__(THREADS, R <= 8 ? 8 : 4) void logprob_bwd_kernel(LogprobBwdLaunch a) {
   constexpr int N = Vec16<T>::N;
   constexpr int NW = THREADS / 64;
   const int tid = threadIdx.x;
@@ -387,6 +299,9 @@ __global__ __launch_bounds__(THREADS, R <= 8 ? 8 : 4) void logprob_bwd_reg_kerne
       const int vi = j * THREADS + tid;
       if (vi < nvec) store(vi, u32x4{0, 0, 0, 0});
     }
+    if constexpr (OVER) {
+      for (int vi = R * THREADS + tid; vi < nvec; vi += THREADS) store(vi, u32x4{0, 0, 0, 0});
+    }
     if (EDGE && tid < n_extra) out[xi] = (T)0.f;
     return;
   }
@@ -414,6 +329,8 @@ __global__ __launch_bounds__(THREADS, R <= 8 ? 8 : 4) void logprob_bwd_reg_kerne
     s_g[j] = a.dseq[a.label_out[it.label_off + j]];
     if (y < 0 || y >= vocab) s_bad = 1;
   }
+  MaxSum over = {kNegInf, 0.f};  // of the vectors past the registers
+  if constexpr (OVER) over = stream_max_sum<T, THREADS>(xv, R * THREADS + tid, nvec);
   // logsumexp of the row from the registers
   float m = kNegInf;
 #pragma unroll
@@ -442,6 +359,7 @@ __global__ __launch_bounds__(THREADS, R <= 8 ? 8 : 4) void logprob_bwd_reg_kerne
     }
   }
   MaxSum acc = {m, s};
+  if constexpr (OVER) acc = combine(acc, over);
   if (EDGE && tid < n_extra) acc = combine(acc, MaxSum{xe, 1.f});
   for (int off = 32; off > 0; off >>= 1) {
     MaxSum o;
@@ -467,28 +385,42 @@ __global__ __launch_bounds__(THREADS, R <= 8 ? 8 : 4) void logprob_bwd_reg_kerne
   const float c = s_c;
   const float lse2 = s_lse * kLog2e;
   const bool bad = s_bad != 0;
+  auto gradient = [&](int vi, const u32x4& x16) {
+    float f[N];
+    Vec16<T>::unpack(x16, f);
+#pragma unroll
+    for (int e = 0; e < N; ++e) f[e] = -c * fast_exp2(fmaf(f[e], kLog2e, -lse2));
+    for (int l = 0; l < cnt; ++l) {
+      const int d = s_y[l] - (head + vi * N);
+      if ((unsigned)d < (unsigned)N) {
+#pragma unroll
+        for (int e = 0; e < N; ++e) f[e] += (e == d) ? s_g[l] : 0.f;
+      }
+    }
+    if (bad) {
+#pragma unroll
+      for (int e = 0; e < N; ++e) f[e] = __builtin_nanf("");
+    }
+    store(vi, Pack16<T>::pack(f));
+  };
+  if constexpr (OVER) {
+    for (int base = R * THREADS + tid; base < nvec; base += THREADS * kLpUnroll) {
+      u32x4 w[kLpUnroll];
+#pragma unroll
+      for (int j = 0; j < kLpUnroll; ++j) {
+        const int vi = base + j * THREADS;
+        w[j] = vi < nvec ? xv[vi] : u32x4{0, 0, 0, 0};
+      }
+#pragma unroll
+      for (int j = 0; j < kLpUnroll; ++j)
+        if (base + j * THREADS < nvec) gradient(base + j * THREADS, w[j]);
+    }
+  }
   opaque(u);
 #pragma unroll
   for (int j = 0; j < R; ++j) {
     const int vi = j * THREADS + tid;
-    if (vi < nvec) {
-      float f[N];
-      Vec16<T>::unpack(u[j], f);
-#pragma unroll
-      for (int e = 0; e < N; ++e) f[e] = -c * fast_exp2(fmaf(f[e], kLog2e, -lse2));
-      for (int l = 0; l < cnt; ++l) {
-        const int d = s_y[l] - (head + vi * N);
-        if ((unsigned)d < (unsigned)N) {
-#pragma unroll
-          for (int e = 0; e < N; ++e) f[e] += (e == d) ? s_g[l] : 0.f;
-        }
-      }
-      if (bad) {
-#pragma unroll
-        for (int e = 0; e < N; ++e) f[e] = __builtin_nanf("");
-      }
-      store(vi, Pack16<T>::pack(f));
-    }
+    if (vi < nvec) gradient(vi, u[j]);
   }
   if (EDGE && tid < n_extra) {
     float f = -c * fast_exp2(fmaf(xe, kLog2e, -lse2));
@@ -650,18 +582,15 @@ hipError_t launch_logprob(const LogprobLaunch& a, hipStream_t s) {
 namespace {
 
 // The shape with the most workgroups per compute unit whose registers hold a row
-// of `nvec` 16-byte vectors; the two-read kernel when none does.
+// of `nvec` 16-byte vectors.
 template <typename T, bool EDGE>
 void launch_logprob_bwd_rows(const LogprobBwdLaunch& a, int grid, int nvec, hipStream_t s) {
   constexpr int kMost = EDGE ? 18 : 19;
-  if (nvec <= 512 * 8)
-    hipLaunchKernelGGL((logprob_bwd_reg_kernel<T, 512, 8, EDGE>), dim3(grid), dim3(512), 0, s, a);
-  else if (nvec <= 1024 * 8)
-    hipLaunchKernelGGL((logprob_bwd_reg_kernel<T, 1024, 8, EDGE>), dim3(grid), dim3(1024), 0, s, a);
-  else if (nvec <= 1024 * kMost)
-    hipLaunchKernelGGL((logprob_bwd_reg_kernel<T, 1024, kMost, EDGE>), dim3(grid), dim3(1024), 0, s, a);
-  else
-    hipLaunchKernelGGL(logprob_bwd_kernel<T>, dim3(grid), dim3(kLpThreads), 0, s, a);
+  auto launch = [&](auto kernel, int threads) { hipLaunchKernelGGL(kernel, dim3(grid), dim3(threads), 0, s, a); };
+  if (nvec <= 512 * 8) launch(logprob_bwd_kernel<T, 512, 8, EDGE, false>, 512);
+  else if (nvec <= 1024 * 8) launch(logprob_bwd_kernel<T, 1024, 8, EDGE, false>, 1024);
+  else if (nvec <= 1024 * kMost) launch(logprob_bwd_kernel<T, 1024, kMost, EDGE, false>, 1024);
+  else launch(logprob_bwd_kernel<T, 1024, 16, EDGE, true>, 1024);
 }
 
 }  // namespace

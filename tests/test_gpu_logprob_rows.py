@@ -1,7 +1,7 @@
 """GPU tests of the log-prob kernels' row shapes: vocabularies at the edges of the
 register-held shapes (512 x 8, 1024 x 8, 1024 x 19 and, for rows that start on no
-16-byte boundary, 1024 x 18 vectors of 16 bytes) and of the two-read kernel, rows
-shorter than a vector, and matrices whose first row is itself off a boundary.
+16-byte boundary, 1024 x 18 vectors of 16 bytes) and of the form that streams what
+1024 x 16 vectors do not hold, rows shorter than a vector, and matrices whose first row is itself off a boundary.
 Labels sit on the first and last elements of the rows, where a head or tail element
 belongs to one thread.  Against the oracle: the scores in fp32 sums (relative error
 a few 1e-6 for 1e5 values, held to 1e-5 of the row's log-prob plus 1e-5), the
@@ -31,7 +31,7 @@ def _at_offset(x, offset):
 
 
 CASES = [(v, BF, 0) for v in (1, 7, 8, 9, 17, 4097, 32768, 32769, 32776, 65536, 65541, 147457, 147465, 155648, 155656)]
-CASES += [(v, F32, 0) for v in (1, 3, 5, 9, 16385, 16388, 32769, 32773, 73729, 73733)]
+CASES += [(v, F32, 0) for v in (1, 3, 5, 9, 16385, 16388, 32769, 32773, 73729, 73733, 77824, 77828, 131075, 300000)]
 CASES += [(4096, BF, 1), (4099, BF, 3), (32776, BF, 7), (4096, F32, 1), (73732, F32, 3)]
 
 
