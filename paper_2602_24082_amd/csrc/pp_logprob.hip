@@ -110,17 +110,18 @@ struct RowSplit {
   __device__ __forceinline__ int extra(int tid) const { return tid < head ? tid : tid + nvec * N; }
 };
 
-// Online (max, sum) over the vectors first, first + THREADS, ... below nvec of one
-// thread, kLpUnroll loads in flight.
+// Online (max, sum) over the vectors first + tid, first + tid + THREADS, ... below
+// nvec of thread tid, kLpUnroll loads in flight.
 template <typename T, int THREADS>
 __device__ __forceinline__ MaxSum stream_max_sum(const u32x4* __restrict__ xv, int first, int nvec) {
+  const int tid = threadIdx.x;
   constexpr int N = Vec16<T>::N;
   MaxSum acc = {kNegInf, 0.f};
   for (int base = first; base < nvec; base += THREADS * kLpUnroll) {
     u32x4 u[kLpUnroll];
 #pragma unroll
     for (int j = 0; j < kLpUnroll; ++j) {
-      const int vi = base + j * THREADS;
+      const int vi = base + j * THREADS + tid;
       u[j] = vi < nvec ? __builtin_nontemporal_load(xv + vi) : u32x4{0, 0, 0, 0};
     }
     float f[kLpUnroll * N];
@@ -129,7 +130,8 @@ __device__ __forceinline__ MaxSum stream_max_sum(const u32x4* __restrict__ xv, i
     float mloc = kNegInf;
 #pragma unroll
     for (int j = 0; j < kLpUnroll; ++j) {
-      if (base + j * THREADS < nvec) {
+      const int vi = base + j * THREADS + tid;
+      if (vi < nvec) {
 #pragma unroll
         for (int e = 0; e < N; ++e) mloc = fmaxf(mloc, f[j * N + e]);
       }
@@ -140,7 +142,8 @@ __device__ __forceinline__ MaxSum stream_max_sum(const u32x4* __restrict__ xv, i
       float s = acc.s * fast_exp2(acc.m * kLog2e - ml);
 #pragma unroll
       for (int j = 0; j < kLpUnroll; ++j) {
-        if (base + j * THREADS < nvec) {
+        const int vi = base + j * THREADS + tid;
+        if (vi < nvec) {
 #pragma unroll
           for (int e = 0; e < N; ++e) s += fast_exp2(fmaf(f[j * N + e], kLog2e, -ml));
         }
@@ -162,7 +165,7 @@ __device__ float row_logsumexp(const T* __restrict__ x, int vocab) {
   const int tid = threadIdx.x;
   const RowSplit<T> rs(x, vocab);
   const float xe = tid < rs.n_extra ? elem<T>(x, rs.extra(tid)) : kNegInf;
-  MaxSum acc = stream_max_sum<T, kLpThreads>(reinterpret_cast<const u32x4*>(x + rs.head), tid, rs.nvec);
+  MaxSum acc = stream_max_sum<T, kLpThreads>(reinterpret_cast<const u32x4*>(x + rs.head), 0, rs.nvec);
   if (tid < rs.n_extra) acc = combine(acc, MaxSum{xe, 1.f});
   // workgroup reduction of (m, s)
   for (int off = 32; off > 0; off >>= 1) {
@@ -330,7 +333,7 @@ __global__ __launch_bounds__(THREADS, R <= 8 ? 8 : 4) void logprob_bwd_kernel(Lo
     if (y < 0 || y >= vocab) s_bad = 1;
   }
   MaxSum over = {kNegInf, 0.f};  // of the vectors past the registers
-  if constexpr (OVER) over = stream_max_sum<T, THREADS>(xv, R * THREADS + tid, nvec);
+  if constexpr (OVER) over = stream_max_sum<T, THREADS>(xv, R * THREADS, nvec);
   // logsumexp of the row from the registers
   float m = kNegInf;
 #pragma unroll
