@@ -14,7 +14,8 @@
 //              responses' contributions in one place.  Per step (S = Q K^T,
 //              lane = key):
 //                P  = exp2(S*scale*log2e - lse_i*log2e) (masked)
-//                dP - delta_i = dO V^T accumulated from -delta_i,  dS = P (dP - delta_i)
+//                dP = dO V^T,  dS = P (dP - delta_i)
+//                (at head size 64 dP accumulates from -delta_i)
 //                dV^T += dO^T P,  dK^T += Q^T dS   (dO^T, Q^T by transposed LDS reads)
 //
 //   stored dS (the default; the workspace holds one bf16 dS value per pair of
@@ -283,6 +284,13 @@ __global__ __launch_bounds__(512, 1) void bwd_dkdv_kernel(BwdParams<TO> p) {
   // them), which halves the row reads of a step: 564 -> 547 us on 30671 tokens of 16
   // heads.  At 128 they would spill.
   constexpr bool kHoldKV = D == 64;
+  // At head size 64 dP's accumulator starts from -delta, read from LDS into place of
+  // the zeros, which spares 16 of the block's 96 vector instructions.  At 128 that
+  // would give 2% of this pass (7.21 -> 7.06 ms on the 72B-shaped long-prefix batch)
+  // but rounds dS once for every product added to -delta: there the sum is formed
+  // first and delta subtracted once.  (At 64 the error against 64 bits is the same
+  // either way: 2.4594e-3 of dK on 24 ragged rows.)
+  constexpr bool kAccDelta = D == 64;
   bf16x8 kf[D / 16], vf[D / 16];
   if constexpr (kHoldKV) {
     wait_vmem<0>();  // this wave's part of K and V (and of the first step) has landed
@@ -323,15 +331,14 @@ __global__ __launch_bounds__(512, 1) void bwd_dkdv_kernel(BwdParams<TO> p) {
     // S = Q K^T and dP = dO V^T over D/16 chunks; the four fragments of chunk
     // c + 1 are read while chunk c's two MFMAs run (the scheduling groups keep
     // the compiler from bunching the reads)
-    // (dP's accumulator starts from -delta, read from LDS into place of the
-    // zeros, which spares 16 of the block's 96 vector instructions: 7.10 -> 7.03 ms
-    // on the 72B-shaped long-prefix batch)
-    f32x16 s = f32x16{}, dp;
+    f32x16 s = f32x16{}, dp = f32x16{};
+    if constexpr (kAccDelta) {
 #pragma unroll
-    for (int r4 = 0; r4 < 4; ++r4) {
-      const f32x4 d4 = *reinterpret_cast<const f32x4*>(&sg.ndelta[qb * 32 + 8 * r4 + 4 * hf]);
+      for (int r4 = 0; r4 < 4; ++r4) {
+        const f32x4 d4 = *reinterpret_cast<const f32x4*>(&sg.ndelta[qb * 32 + 8 * r4 + 4 * hf]);
 #pragma unroll
-      for (int e = 0; e < 4; ++e) dp[4 * r4 + e] = d4[e];
+        for (int e = 0; e < 4; ++e) dp[4 * r4 + e] = d4[e];
+      }
     }
     {
       constexpr int NC = D / 16;
@@ -350,7 +357,7 @@ __global__ __launch_bounds__(512, 1) void bwd_dkdv_kernel(BwdParams<TO> p) {
         dp = mfma32(fo[c & 1], kHoldKV ? vf[c] : fv[c & 1], dp);
       }
       constexpr int RD = kHoldKV ? 1 : 2;  // reads ahead of each MFMA
-      __builtin_amdgcn_sched_group_barrier(kSchedDsRead, 4 + 2 * RD, 0);
+      __builtin_amdgcn_sched_group_barrier(kSchedDsRead, (kAccDelta ? 4 : 0) + 2 * RD, 0);
 #pragma unroll
       for (int c = 0; c < NC; ++c) {
         // two reads of the next chunk before each MFMA: LDS requests spread
@@ -377,12 +384,14 @@ __global__ __launch_bounds__(512, 1) void bwd_dkdv_kernel(BwdParams<TO> p) {
     for (int r4 = 0; r4 < 4; ++r4) {
       const int il = qb * 32 + 8 * r4 + 4 * hf;
       const f32x4 l4 = *reinterpret_cast<const f32x4*>(&sg.nlse2[il]);
+      f32x4 d4 = f32x4{};
+      if constexpr (!kAccDelta) d4 = *reinterpret_cast<const f32x4*>(&sg.ndelta[il]);
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
         const int r = 4 * r4 + e;
         const float pr = fast_exp2(fmaf(s[r], p.scale_log2, l4[e]));
         s[r] = pr;
-        dp[r] *= pr;
+        dp[r] = pr * (kAccDelta ? dp[r] : dp[r] + d4[e]);
       }
     }
     const bf16x8 pb0 = acc_half_to_bf16(s, 0), pb1 = acc_half_to_bf16(s, 1);
