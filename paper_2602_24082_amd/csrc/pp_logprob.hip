@@ -41,6 +41,10 @@ constexpr int kLpUnroll = PP_LP_UNROLL;  // 16-byte vectors in flight per thread
 
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
+// The larger of two, NaN if either is: a NaN logit makes its row's maximum NaN, and so
+// its sum (fmaxf would pass over it).
+__device__ __forceinline__ float max_or_nan(float a, float b) { return __builtin_elementwise_maximum(a, b); }
+
 // Online (max, sum 2^(x*log2e - m*log2e)) accumulator.
 struct MaxSum {
   float m;  // running max of x (natural units)
@@ -48,10 +52,9 @@ struct MaxSum {
 };
 
 __device__ __forceinline__ MaxSum combine(MaxSum a, MaxSum b) {
-  const float m = fmaxf(a.m, b.m);
+  const float m = max_or_nan(a.m, b.m);
   if (m == kNegInf) return {kNegInf, 0.f};
-  const float s = a.s * fast_exp2((a.m - m) * kLog2e) + b.s * fast_exp2((b.m - m) * kLog2e);
-  return {m, s};
+  return {m, fmaf(a.s, fast_exp2((a.m - m) * kLog2e), b.s * fast_exp2((b.m - m) * kLog2e))};
 }
 
 template <typename T>
@@ -133,10 +136,10 @@ __device__ __forceinline__ MaxSum stream_max_sum(const u32x4* __restrict__ xv, i
       const int vi = base + j * THREADS + tid;
       if (vi < nvec) {
 #pragma unroll
-        for (int e = 0; e < N; ++e) mloc = fmaxf(mloc, f[j * N + e]);
+        for (int e = 0; e < N; ++e) mloc = max_or_nan(mloc, f[j * N + e]);
       }
     }
-    const float m = fmaxf(acc.m, mloc);
+    const float m = max_or_nan(acc.m, mloc);
     if (m != kNegInf) {
       const float ml = m * kLog2e;
       float s = acc.s * fast_exp2(acc.m * kLog2e - ml);
@@ -154,29 +157,53 @@ __device__ __forceinline__ MaxSum stream_max_sum(const u32x4* __restrict__ xv, i
   return acc;
 }
 
-// ln sum_v exp(x[v]) of one logit row, for every thread of a kLpThreads
-// workgroup: one streaming pass of aligned 16-byte loads (kLpUnroll in flight per
-// thread) keeping an online (max, sum) per thread, the row's head and tail
-// elements last, then a fixed-order workgroup combine.  HBM bound.  Rows that
-// start on no 16-byte boundary used to be read element by element: 2224 rows of
-// 50257 fp32 took 135 us and take 69 us (6.5 TB/s).
-template <typename T>
-__device__ float row_logsumexp(const T* __restrict__ x, int vocab) {
-  const int tid = threadIdx.x;
-  const RowSplit<T> rs(x, vocab);
-  const float xe = tid < rs.n_extra ? elem<T>(x, rs.extra(tid)) : kNegInf;
-  MaxSum acc = stream_max_sum<T, kLpThreads>(reinterpret_cast<const u32x4*>(x + rs.head), 0, rs.nvec);
-  if (tid < rs.n_extra) acc = combine(acc, MaxSum{xe, 1.f});
-  // workgroup reduction of (m, s)
+// (max, sum) of all the row for any values, with a difference to the maximum so far
+// for every element: what a workgroup does again when the fast form below does not
+// hold.  Little code, slow and rare.
+template <typename T, int THREADS>
+__device__ __forceinline__ MaxSum any_max_sum(const u32x4* __restrict__ xv, int nvec) {
+  constexpr int N = Vec16<T>::N;
+  MaxSum acc = {kNegInf, 0.f};
+#pragma unroll 1
+  for (int vi = threadIdx.x; vi < nvec; vi += THREADS) {
+    float f[N];
+    Vec16<T>::unpack(xv[vi], f);
+#pragma unroll
+    for (int e = 0; e < N; ++e) acc = combine(acc, MaxSum{f[e], 1.f});
+  }
+  return acc;
+}
+
+// A row's logsumexp, lse = m + ln s rounded.
+struct RowLse {
+  float m, s, lse;
+  // exp(x - m) as one fma and one exp2, 2^(x*log2e - m*log2e), needs m*log2e to be
+  // finite.  A maximum out there is far: a type's lowest value in every masked entry, as
+  // masks are often written, or its largest.  A thread that met nothing but such values
+  // makes s infinite or NaN (lowest) or 0 (largest).
+  __device__ __forceinline__ bool far() const { return fabsf(m) >= 1e38f && fabsf(m) < __builtin_huge_valf(); }
+  __device__ __forceinline__ bool redo() const {
+    return fabsf(m) < __builtin_huge_valf() && (far() || !(s < __builtin_huge_valf()));
+  }
+  // Where m is so large that lse no longer holds ln s, differences to it are formed part
+  // by part.
+  __device__ __forceinline__ float log_prob(float x) const { return far() ? (x - m) - logf(s) : x - lse; }
+  __device__ __forceinline__ float far_softmax(float x) const { return fast_exp2(((x - m) - logf(s)) * kLog2e); }
+};
+
+// The workgroup's (max, sum)s combined in a fixed order, for every thread.  `work` is
+// run by thread 0 beside the last step.
+template <int THREADS, typename Work>
+__device__ __forceinline__ RowLse block_lse(MaxSum acc, Work&& work) {
   for (int off = 32; off > 0; off >>= 1) {
     MaxSum o;
     o.m = __shfl_xor(acc.m, off, 64);
     o.s = __shfl_xor(acc.s, off, 64);
     acc = combine(acc, o);
   }
-  __shared__ float sm[kLpThreads / 64], ss[kLpThreads / 64];
-  __shared__ float s_lse;
-  const int wave = tid >> 6, lane = tid & 63;
+  __shared__ float sm[THREADS / 64], ss[THREADS / 64];
+  __shared__ RowLse s_lse;
+  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
   if (lane == 0) {
     sm[wave] = acc.m;
     ss[wave] = acc.s;
@@ -184,11 +211,36 @@ __device__ float row_logsumexp(const T* __restrict__ x, int vocab) {
   __syncthreads();
   if (tid == 0) {
     MaxSum t = {sm[0], ss[0]};
-    for (int w = 1; w < kLpThreads / 64; ++w) t = combine(t, MaxSum{sm[w], ss[w]});
-    s_lse = t.m + logf(t.s);
+    for (int w = 1; w < THREADS / 64; ++w) t = combine(t, MaxSum{sm[w], ss[w]});
+    s_lse = {t.m, t.s, t.m + logf(t.s)};
+    work();
   }
   __syncthreads();
   return s_lse;
+}
+
+// ln sum_v exp(x[v]) of one logit row, for every thread of a kLpThreads
+// workgroup: one streaming pass of aligned 16-byte loads (kLpUnroll in flight per
+// thread) keeping an online (max, sum) per thread, the row's head and tail
+// elements last, then a fixed-order workgroup combine.  HBM bound.  Rows that
+// start on no 16-byte boundary used to be read element by element: 2224 rows of
+// 50257 fp32 took 135 us and take 69 us (6.5 TB/s).
+template <typename T>
+__device__ RowLse row_logsumexp(const T* __restrict__ x, int vocab) {
+  const int tid = threadIdx.x;
+  const RowSplit<T> rs(x, vocab);
+  const float xe = tid < rs.n_extra ? elem<T>(x, rs.extra(tid)) : kNegInf;
+  const u32x4* xv = reinterpret_cast<const u32x4*>(x + rs.head);
+  MaxSum acc = stream_max_sum<T, kLpThreads>(xv, 0, rs.nvec);
+  if (tid < rs.n_extra) acc = combine(acc, MaxSum{xe, 1.f});
+  RowLse r = block_lse<kLpThreads>(acc, [] {});
+  if (r.redo()) {
+    acc = any_max_sum<T, kLpThreads>(xv, rs.nvec);
+    if (tid < rs.n_extra) acc = combine(acc, MaxSum{xe, 1.f});
+    __syncthreads();
+    r = block_lse<kLpThreads>(acc, [] {});
+  }
+  return r;
 }
 
 template <typename T>
@@ -198,11 +250,11 @@ __global__ __launch_bounds__(kLpThreads) void logprob_rows_kernel(
     float* __restrict__ tok, int vocab) {
   const LogitRowItem it = rows[blockIdx.x];
   const T* x = logits + it.logit_row * (int64_t)vocab;
-  const float lse = row_logsumexp<T>(x, vocab);
+  const RowLse lse = row_logsumexp<T>(x, vocab);
   for (int j = threadIdx.x; j < it.label_cnt; j += kLpThreads) {
     const int32_t pos = labels[it.label_off + j];
     const int32_t y = tokens[pos];
-    tok[pos] = (y >= 0 && y < vocab) ? elem<T>(x, y) - lse : __builtin_nanf("");
+    tok[pos] = (y >= 0 && y < vocab) ? lse.log_prob(elem<T>(x, y)) : __builtin_nanf("");
   }
 }
 
@@ -273,7 +325,6 @@ __device__ __forceinline__ void opaque(u32x4 (&u)[R]) {
 template <typename T, int THREADS, int R, bool EDGE, bool OVER>
 __global__ __launch_bounds__(THREADS, R <= 8 ? 8 : 4) void logprob_bwd_kernel(LogprobBwdLaunch a) {
   constexpr int N = Vec16<T>::N;
-  constexpr int NW = THREADS / 64;
   const int tid = threadIdx.x;
   const int vocab = a.vocab;
   // dense: workgroup = flat logit row r, output row r; gathered: workgroup =
@@ -320,8 +371,7 @@ __global__ __launch_bounds__(THREADS, R <= 8 ? 8 : 4) void logprob_bwd_kernel(Lo
   const LogitRowItem it = a.rows[item];
   __shared__ int s_y[kMaxRowLabels];
   __shared__ float s_g[kMaxRowLabels];
-  __shared__ float s_m[NW], s_s[NW];
-  __shared__ float s_c, s_lse;
+  __shared__ float s_c;
   __shared__ int s_bad;
   const int cnt = it.label_cnt;
   if (tid == 0) s_bad = 0;
@@ -342,7 +392,7 @@ __global__ __launch_bounds__(THREADS, R <= 8 ? 8 : 4) void logprob_bwd_kernel(Lo
       float f[N];
       Vec16<T>::unpack(u[j], f);
 #pragma unroll
-      for (int e = 0; e < N; ++e) m = fmaxf(m, f[e]);
+      for (int e = 0; e < N; ++e) m = max_or_nan(m, f[e]);
     }
   }
   // the packed vectors count as rewritten here, so each pass below unpacks
@@ -364,35 +414,17 @@ __global__ __launch_bounds__(THREADS, R <= 8 ? 8 : 4) void logprob_bwd_kernel(Lo
   MaxSum acc = {m, s};
   if constexpr (OVER) acc = combine(acc, over);
   if (EDGE && tid < n_extra) acc = combine(acc, MaxSum{xe, 1.f});
-  for (int off = 32; off > 0; off >>= 1) {
-    MaxSum o;
-    o.m = __shfl_xor(acc.m, off, 64);
-    o.s = __shfl_xor(acc.s, off, 64);
-    acc = combine(acc, o);
-  }
-  const int wave = tid >> 6, lane = tid & 63;
-  if (lane == 0) {
-    s_m[wave] = acc.m;
-    s_s[wave] = acc.s;
-  }
-  __syncthreads();
-  if (tid == 0) {
-    MaxSum w = {s_m[0], s_s[0]};
-    for (int i = 1; i < NW; ++i) w = combine(w, MaxSum{s_m[i], s_s[i]});
-    s_lse = w.m + logf(w.s);
+  RowLse lse = block_lse<THREADS>(acc, [&] {
     float c = 0.f;
     for (int j = 0; j < cnt; ++j) c += s_g[j];
     s_c = c;
-  }
-  __syncthreads();
+  });
   const float c = s_c;
-  const float lse2 = s_lse * kLog2e;
+  const float lse2 = lse.lse * kLog2e;
   const bool bad = s_bad != 0;
-  auto gradient = [&](int vi, const u32x4& x16) {
-    float f[N];
-    Vec16<T>::unpack(x16, f);
+  auto finish = [&](int vi, float* f) {  // f: the softmax of vector vi
 #pragma unroll
-    for (int e = 0; e < N; ++e) f[e] = -c * fast_exp2(fmaf(f[e], kLog2e, -lse2));
+    for (int e = 0; e < N; ++e) f[e] *= -c;
     for (int l = 0; l < cnt; ++l) {
       const int d = s_y[l] - (head + vi * N);
       if ((unsigned)d < (unsigned)N) {
@@ -405,6 +437,34 @@ __global__ __launch_bounds__(THREADS, R <= 8 ? 8 : 4) void logprob_bwd_kernel(Lo
       for (int e = 0; e < N; ++e) f[e] = __builtin_nanf("");
     }
     store(vi, Pack16<T>::pack(f));
+  };
+  auto finish_extra = [&](float softmax) {
+    float f = -c * softmax;
+    for (int l = 0; l < cnt; ++l) f += s_y[l] == xi ? s_g[l] : 0.f;
+    out[xi] = (T)(bad ? __builtin_nanf("") : f);
+  };
+  if (__builtin_expect(__builtin_amdgcn_readfirstlane(lse.redo() ? 1 : 0), 0)) {
+    acc = any_max_sum<T, THREADS>(xv, nvec);
+    if (EDGE && tid < n_extra) acc = combine(acc, MaxSum{xe, 1.f});
+    __syncthreads();
+    lse = block_lse<THREADS>(acc, [] {});
+#pragma unroll 1
+    for (int vi = tid; vi < nvec; vi += THREADS) {
+      float f[N];
+      Vec16<T>::unpack(xv[vi], f);
+#pragma unroll
+      for (int e = 0; e < N; ++e) f[e] = lse.far_softmax(f[e]);
+      finish(vi, f);
+    }
+    if (EDGE && tid < n_extra) finish_extra(lse.far_softmax(xe));
+    return;
+  }
+  auto gradient = [&](int vi, const u32x4& x16) {
+    float f[N];
+    Vec16<T>::unpack(x16, f);
+#pragma unroll
+    for (int e = 0; e < N; ++e) f[e] = fast_exp2(fmaf(f[e], kLog2e, -lse2));
+    finish(vi, f);
   };
   if constexpr (OVER) {
     for (int base = R * THREADS + tid; base < nvec; base += THREADS * kLpUnroll) {
@@ -425,11 +485,7 @@ __global__ __launch_bounds__(THREADS, R <= 8 ? 8 : 4) void logprob_bwd_kernel(Lo
     const int vi = j * THREADS + tid;
     if (vi < nvec) gradient(vi, u[j]);
   }
-  if (EDGE && tid < n_extra) {
-    float f = -c * fast_exp2(fmaf(xe, kLog2e, -lse2));
-    for (int l = 0; l < cnt; ++l) f += s_y[l] == xi ? s_g[l] : 0.f;
-    out[xi] = (T)(bad ? __builtin_nanf("") : f);
-  }
+  if (EDGE && tid < n_extra) finish_extra(fast_exp2(fmaf(xe, kLog2e, -lse2)));
 }
 
 // One wave per (row, response) slot; lane l sums tokens l, l+64, ... in order,
