@@ -117,7 +117,8 @@ typedef struct pp_pack_desc {
  * inputs need room for their bf16 copies).  vocab is used only for logprob and
  * may be 0.  hq, hkv and head_dim are validated as for pp_attn_fwd when fwd or
  * bwd is requested.  bwd is the workspace of pp_attn_bwd / pp_attn_bwd_rope in
- * their default (recompute) mode; pp_bwd_stored_ds_workspace_size gives the
+ * their default (recompute) mode (its partial sums included; they also take
+ * less, see there); pp_bwd_stored_ds_workspace_size gives the
  * larger one of the stored-dS mode.  logprob serves both pp_seq_logprob and
  * pp_seq_logprob_bwd.  loss is the workspace of pp_dpo_loss for this batch's B. */
 pp_status pp_workspace_size(const pp_pack_desc* desc, pp_dtype dtype, int hq, int hkv, int head_dim,
@@ -150,15 +151,21 @@ pp_status pp_attn_fwd(const pp_pack_desc* desc, pp_dtype dtype, int hq, int hkv,
  * the input dtype; padding rows are written as 0.  The result is deterministic
  * (no atomics).  Errors as pp_attn_fwd.
  *
- * Workspace and mode: with ws_bytes >= pp_workspace_size's bwd the dQ pass
- * recomputes S and dP (scratch linear in the tokens, as Sec. 3.2.1's memory
- * argument assumes; a batch of few key tiles adds fp32 partial sums of dK and dV,
- * at most a few hundred tiles of 128 keys, so that the whole chip works on it).  With ws_bytes >= pp_bwd_stored_ds_workspace_size's bwd
- * the key-major pass also stores dS (bf16, one value per query-key pair of
- * every 32 x 32 block with a visible pair, per query head) at the end of the
- * workspace and the dQ pass reads it back instead, so S, P and dP are computed
- * once.  Both modes round dS to bf16 before the products that use it; they agree
- * to fp32 rounding.  Below pp_workspace_size's bwd: PP_ERR_WORKSPACE_TOO_SMALL. */
+ * Workspace and mode.  What every call needs is linear in the tokens, as
+ * Sec. 3.2.1's memory argument assumes.  pp_workspace_size's bwd is that, plus,
+ * for a batch of few key tiles, room for fp32 partial sums of dK and dV with
+ * which the whole chip works on it (at most 768 tiles of 128 keys of one kv-head:
+ * 96 MiB at head_dim 128, 48 MiB at 64; so a smaller batch may report more bytes
+ * than a larger one).  A workspace without room for the partial sums is used
+ * without them.  With ws_bytes >= pp_bwd_stored_ds_workspace_size's bwd (or that
+ * less the partial sums) the key-major pass also stores dS (bf16, one value per
+ * query-key pair of every 32 x 32 block with a visible pair, per query head) at
+ * the end of the workspace and the dQ pass reads it back instead of recomputing S
+ * and dP, so S, P and dP are computed once; where the partial sums are larger than
+ * dS, a workspace with room for either but not both takes the partial sums.  Both
+ * modes round dS to bf16 before the products that use it; they agree to fp32
+ * rounding, as do results with and without the partial sums (their sums are added
+ * in another order).  Below the linear part: PP_ERR_WORKSPACE_TOO_SMALL. */
 pp_status pp_attn_bwd(const pp_pack_desc* desc, pp_dtype dtype, int hq, int hkv, int head_dim,
                       float scale, const void* q, const void* k, const void* v, const void* o,
                       const float* lse, const void* dout, void* dq, void* dk, void* dv, void* ws,
@@ -256,22 +263,24 @@ pp_status pp_attn_bwd_rope(const pp_pack_desc* desc, pp_dtype dtype, int hq, int
 typedef struct pp_plan pp_plan;
 
 /* Workspace bytes of a plan for this pack and shape (forward and backward
- * metadata and the backward's scratch, for the recompute backward).  Errors as
- * pp_attn_fwd. */
+ * metadata and the backward's scratch, for the recompute backward; its partial
+ * sums included, see pp_attn_bwd).  Errors as pp_attn_fwd. */
 pp_status pp_plan_workspace_size(const pp_pack_desc* desc, pp_dtype dtype, int hq, int hkv, int head_dim,
                                  size_t* bytes);
 
 /* The larger workspaces that select the backward's stored-dS mode (see
  * pp_attn_bwd): *bwd for pp_attn_bwd / pp_attn_bwd_rope, *plan for
- * pp_plan_create (a plan made with at least this many bytes stores dS).
+ * pp_plan_create (a plan made with at least this many bytes stores dS); the
+ * partial sums of pp_attn_bwd are included.
  * Either pointer may be NULL.  Errors as pp_attn_fwd, plus PP_ERR_UNSUPPORTED
  * when the batch has 2^31 or more stored tiles per head. */
 pp_status pp_bwd_stored_ds_workspace_size(const pp_pack_desc* desc, pp_dtype dtype, int hq, int hkv, int head_dim,
                                           size_t* bwd, size_t* plan);
 
-/* Builds a plan and enqueues its metadata copy into ws (dev, ws_bytes >=
- * pp_plan_workspace_size's bytes, or >= pp_bwd_stored_ds_workspace_size's plan
- * for the stored-dS backward) on hip_stream.  rope_base (host, may be NULL)
+/* Builds a plan and enqueues its metadata copy into ws (dev, ws_bytes as
+ * pp_plan_workspace_size's bytes, or as pp_bwd_stored_ds_workspace_size's plan
+ * for the stored-dS backward; less the partial sums is taken too, as by
+ * pp_attn_bwd) on hip_stream.  rope_base (host, may be NULL)
  * selects the rotary variants.  *plan receives the handle, or NULL on error.
  * Errors as pp_attn_fwd, plus PP_ERR_INVALID_ARGUMENT for a NULL plan pointer
  * or a bad rope_base. */

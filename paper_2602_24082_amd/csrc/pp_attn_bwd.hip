@@ -70,6 +70,7 @@ struct BwdParams {
   const QTileItem* dq_items;
   const KTileEntry* dq_ktiles;
   const KTileItem* kv_items;
+  const KTilePart* kv_parts;
   const KTileSplit* kv_splits;
   float* kv_part;  // fp32 partial dK, dV of the cut key tiles: [slot][kv-head][2][4 key blocks][32 * D]
   const int32_t* seg_lo;
@@ -221,7 +222,14 @@ __global__ __launch_bounds__(512, 1) void bwd_dkdv_kernel(BwdParams<TO> p) {
 
   const int nq = it.q_end - it.q_begin;
   const int nsteps = (nq + KBM - 1) / KBM;
-  const int n_iter = it.n_end;
+  // the pairs this item walks, and the slot of its sums (-1: the whole tile)
+  int n_first = 0, n_iter = G * nsteps, slot = -1;
+  if (it.part >= 0) {
+    const KTilePart pt = load_uniform(p.kv_parts + it.part);
+    n_first = pt.n_begin;
+    n_iter = pt.n_end;
+    slot = pt.slot;
+  }
   const int64_t q_stride = (int64_t)p.hq * D;
   const int64_t kv_stride = (int64_t)p.hkv * D;
 
@@ -243,9 +251,9 @@ __global__ __launch_bounds__(512, 1) void bwd_dkdv_kernel(BwdParams<TO> p) {
   Dma dma;
   dma.init(wave * (KBM / 8), q_stride, lane);
   int f_hh = 0, f_stp = 0;  // next step to fetch
-  if (it.n_begin > 0) {
-    f_hh = it.n_begin / nsteps;
-    f_stp = it.n_begin - f_hh * nsteps;
+  if (n_first > 0) {
+    f_hh = n_first / nsteps;
+    f_stp = n_first - f_hh * nsteps;
   }
   int c_hh = f_hh;  // head, within the kv-head's group, and first query of the step before the first
   int qs = it.q_begin + (f_stp - 1) * KBM;
@@ -265,7 +273,7 @@ __global__ __launch_bounds__(512, 1) void bwd_dkdv_kernel(BwdParams<TO> p) {
       ++f_hh;
     }
   };
-  if (it.n_begin < n_iter) issue(it.n_begin);
+  if (n_first < n_iter) issue(n_first);
 
   f32x16 acc_dk[D / 32], acc_dv[D / 32];
 #pragma unroll
@@ -303,7 +311,7 @@ __global__ __launch_bounds__(512, 1) void bwd_dkdv_kernel(BwdParams<TO> p) {
   }
   bool stored = false;  // this wave's last step ended with its two dS stores
 
-  for (int n = it.n_begin; n < n_iter; ++n) {
+  for (int n = n_first; n < n_iter; ++n) {
     if (qs + KBM == it.q_begin + nsteps * KBM) {
       qs = it.q_begin;
       ++c_hh;
@@ -417,7 +425,7 @@ __global__ __launch_bounds__(512, 1) void bwd_dkdv_kernel(BwdParams<TO> p) {
   wait_vmem<0>();  // a tile of padding keys has no steps: its K/V DMA is still owed
   // add the second query half's partials into the first half's waves: first dK, then dV
   float* red = sm.red[kb];
-  if (it.slot >= 0) {
+  if (slot >= 0) {
     // a part of a cut tile: the sums go out as they lie in the accumulators
 #pragma unroll
     for (int pass = 0; pass < 2; ++pass) {
@@ -431,7 +439,7 @@ __global__ __launch_bounds__(512, 1) void bwd_dkdv_kernel(BwdParams<TO> p) {
       }
       __syncthreads();
       if (qb == 0) {
-        float* part = p.kv_part + ((((int64_t)it.slot * p.hkv + g) * 2 + pass) * 4 + kb) * (32 * D);
+        float* part = p.kv_part + ((((int64_t)slot * p.hkv + g) * 2 + pass) * 4 + kb) * (32 * D);
 #pragma unroll
         for (int m = 0; m < D / 32; ++m)
 #pragma unroll
@@ -952,6 +960,7 @@ hipError_t launch_bwd_t(const AttnBwdLaunch& a, hipStream_t s) {
   p.dq_items = a.dq_items;
   p.dq_ktiles = a.dq_ktiles;
   p.kv_items = a.kv_items;
+  p.kv_parts = a.kv_parts;
   p.kv_splits = a.kv_splits;
   p.kv_part = a.kv_part;
   p.seg_lo = a.seg_lo;

@@ -276,8 +276,11 @@ int32_t key_tile_q_end(const Row& r, int32_t k0, int32_t k_end) {
   return end;
 }
 
+// (head, step) pairs of a key tile.
+inline int tile_pairs(const KTileItem& t, int G) { return G * ((t.q_end - t.q_begin + kBwdBlockM - 1) / kBwdBlockM); }
+
 // Key tiles of the dK/dV pass, each one work item, longest first.
-void build_kplan(const Batch& bt, int BN, int G, std::vector<KTileItem>* out) {
+void build_kplan(const Batch& bt, int BN, std::vector<KTileItem>* out) {
   out->clear();
   for (int b = 0; b < bt.B; ++b) {
     const Row& r = bt.rows[b];
@@ -294,15 +297,12 @@ void build_kplan(const Batch& bt, int BN, int G, std::vector<KTileItem>* out) {
         it.q_begin = k0;  // query k0 sees key k0
         it.q_end = key_tile_q_end(r, k0, it.k_end);
       }
-      it.n_begin = 0;
-      it.n_end = G * ((it.q_end - it.q_begin + kBwdBlockM - 1) / kBwdBlockM);
-      it.slot = -1;
+      it.part = -1;
       out->push_back(it);
     }
   }
-  std::stable_sort(out->begin(), out->end(), [](const KTileItem& a, const KTileItem& b) {
-    return a.n_end - a.n_begin > b.n_end - b.n_begin;
-  });
+  std::stable_sort(out->begin(), out->end(),
+                   [](const KTileItem& a, const KTileItem& b) { return tile_pairs(a, 1) > tile_pairs(b, 1); });
 }
 
 // Parts of a tile of n (head, step) pairs when no part may exceed `most`.
@@ -311,14 +311,14 @@ inline int split_parts(int n, int most) { return most > 0 && n > most ? (n + mos
 // Finish time, in steps, of one kv-head's items (longest first, each tile cut
 // so that no part exceeds `most` steps; 0: none) on `units` compute units that
 // each take the next item when they are free, and the parts of cut tiles.
-double kplan_span(const std::vector<KTileItem>& tiles, int most, int units, int* n_parts) {
+double kplan_span(const std::vector<KTileItem>& tiles, int G, int most, int units, int* n_parts) {
   // in steps of kBwdBlockM queries (2.0 us at head size 128, measured on 8B-shaped rows): 1.6 for a workgroup's K/V
   // load and epilogue, 1 more to write a part's fp32 sums
   constexpr double kItem = 1.6, kPart = 1.0;
   std::vector<std::pair<int, bool>> items;  // steps, part of a cut tile
   *n_parts = 0;
   for (const KTileItem& t : tiles) {
-    const int n = t.n_end - t.n_begin, parts = split_parts(n, most);
+    const int n = tile_pairs(t, G), parts = split_parts(n, most);
     if (parts > 1) *n_parts += parts;
     for (int i = 0; i < parts; ++i) items.emplace_back((int)((int64_t)n * (i + 1) / parts - (int64_t)n * i / parts), parts > 1);
   }
@@ -334,6 +334,17 @@ double kplan_span(const std::vector<KTileItem>& tiles, int most, int units, int*
   return span;
 }
 
+// The dK/dV pass's items with the longest key tiles cut.
+struct KvCut {
+  std::vector<KTileItem> items;  // longest first; empty: the tiles stay whole
+  std::vector<KTilePart> parts;
+  std::vector<KTileSplit> splits;
+  int slots = 0;
+};
+
+// Bytes of one (slot, kv-head)'s partial dK and dV.
+inline size_t kv_part_bytes(int d) { return (size_t)2 * kBwdBlockN * d * 4; }
+
 // Cuts the longest key tiles of a batch that leaves compute units idle: with
 // few rows a prompt's first tile, which every later query of every head sees,
 // outlasts all others (one 8B-shaped row of 2111 tokens: 17 tiles x 8 kv-heads
@@ -347,49 +358,48 @@ double kplan_span(const std::vector<KTileItem>& tiles, int most, int units, int*
 // has to shorten it by a tenth.  On that row the pass took 201 us whole and takes
 // 89 us cut (53 parts), plus 10 to 15 us for the sums; a rule of even shares, halves
 // and thirds of them took 101 us (67 parts).  One row of 4200 tokens: 324 -> 298 us.
-void split_kplan(int hkv, std::vector<KTileItem>* kv, std::vector<KTileSplit>* splits, int* slots) {
+//
+// Cuts into more than kMaxKvParts parts (96 MiB of sums at head size 128) are left out.
+void split_kplan(const std::vector<KTileItem>& kv, int G, int hkv, KvCut* cut) {
   constexpr double kLaunch = 2.5, kPartsPerStep = 46.0;
-  splits->clear();
-  *slots = 0;
-  if (kv->empty() || (int64_t)kv->size() * hkv > 2 * kComputeUnits) return;
+  *cut = KvCut();
+  if (kv.empty() || (int64_t)kv.size() * hkv > 2 * kComputeUnits) return;
   const int units = std::max(1, kComputeUnits / hkv);
   int64_t work = 0;
-  for (const KTileItem& t : *kv) work += t.n_end - t.n_begin;
-  const int even = (int)((work + units - 1) / units);
-  if ((*kv)[0].n_end < 8 || (*kv)[0].n_end <= even) return;  // the units' even share is the longer
+  for (const KTileItem& t : kv) work += tile_pairs(t, G);
+  const int even = (int)((work + units - 1) / units), longest = tile_pairs(kv[0], G);
+  if (longest < 8 || longest <= even) return;  // the units' even share is the longer
   int parts = 0;
-  const double whole = kplan_span(*kv, 0, units, &parts);
+  const double whole = kplan_span(kv, G, 0, units, &parts);
   double best = whole;
   int most = 0;
   for (int sixths : {9, 6, 4, 3, 2}) {
     const int m = std::max(4, (even * sixths + 5) / 6);
-    const double s = kplan_span(*kv, m, units, &parts) + kLaunch + (double)parts * hkv / kPartsPerStep;
-    if (s < best) {
-      best = s;
+    const double span = kplan_span(kv, G, m, units, &parts) + kLaunch + (double)parts * hkv / kPartsPerStep;
+    if (span < best && (int64_t)parts * hkv <= kMaxKvParts) {
+      best = span;
       most = m;
     }
   }
   if (most == 0 || best > 0.9 * whole) return;
-  std::vector<KTileItem> out;
-  for (const KTileItem& t : *kv) {
-    const int n = t.n_end - t.n_begin, parts = split_parts(n, most);
-    if (parts == 1) {
-      out.push_back(t);
+  std::vector<std::pair<int, KTileItem>> items;  // pairs, item
+  for (const KTileItem& t : kv) {
+    const int n = tile_pairs(t, G), k = split_parts(n, most);
+    if (k == 1) {
+      items.emplace_back(n, t);
       continue;
     }
-    splits->push_back(KTileSplit{t.tok0, t.k0, t.k_end, *slots, parts, 0});
-    for (int i = 0; i < parts; ++i) {
-      KTileItem p = t;
-      p.n_begin = (int32_t)((int64_t)n * i / parts);
-      p.n_end = (int32_t)((int64_t)n * (i + 1) / parts);
-      p.slot = (*slots)++;
-      out.push_back(p);
+    cut->splits.push_back(KTileSplit{t.tok0, t.k0, t.k_end, cut->slots, k, 0});
+    for (int i = 0; i < k; ++i) {
+      const KTilePart p{(int32_t)((int64_t)n * i / k), (int32_t)((int64_t)n * (i + 1) / k), cut->slots++, 0};
+      KTileItem it = t;
+      it.part = (int32_t)cut->parts.size();
+      cut->parts.push_back(p);
+      items.emplace_back(p.n_end - p.n_begin, it);
     }
   }
-  std::stable_sort(out.begin(), out.end(), [](const KTileItem& a, const KTileItem& b) {
-    return a.n_end - a.n_begin > b.n_end - b.n_begin;
-  });
-  kv->swap(out);
+  std::stable_sort(items.begin(), items.end(), [](const auto& a, const auto& b) { return a.first > b.first; });
+  for (const auto& it : items) cut->items.push_back(it.second);
 }
 
 // The per-token arrays below are filled segment by segment: a validated row is
@@ -746,37 +756,47 @@ void plan_fwd(const Batch& bt, pp_dtype dtype, int hq, int hkv, int d, FwdPlan* 
   }
 }
 
-// The backward's workspace ends with the stored-dS region (hq x ds_tiles
-// tiles of 32 x 32 bf16): a workspace that holds it (lay.total bytes) selects
-// the stored-dS mode, one that stops before it (lean_total) the recompute mode.
+// The backward's workspace: its linear part (metadata, per-token scratch, fp32
+// callers' bf16 copies), which every call needs, and two regions that it uses if the
+// workspace has room: the partial sums of cut key tiles, and last the stored dS
+// (hq x ds_tiles tiles of 32 x 32 bf16).  A workspace that holds the linear part and
+// the stored dS selects the stored-dS mode, whether or not there is room for the
+// partial sums too; a smaller one the recompute mode.  In a batch so small that the
+// partial sums are larger than its dS, a workspace with room for one of the two
+// takes the partial sums if they fit (the recompute mode's own size must select it).
 struct BwdPlan {
   QPlan dq;
-  std::vector<KTileItem> kv;
-  std::vector<KTileSplit> kv_splits;
-  int kv_slots = 0;  // partial-sum slots of the cut key tiles
+  std::vector<KTileItem> kv;  // whole key tiles
+  KvCut cut;                  // the same with the longest ones cut, if that pays
   std::vector<int32_t> row_kb0;
   std::vector<DsPanel> panels;
   int64_t ds_tiles = 0;  // per head; -1: the stored mode is not offered
+  // workspace bytes without and with the partial sums (the same if no tile is cut)
+  size_t lean_total[2], stored_total[2];
+  // set for the workspace at hand by settle_bwd
+  bool use_cut = false, store_ds = false;
   Layout lay;
-  size_t r_seg, r_seg_hi, r_dq_items, r_dq_kt, r_kv_items, r_kv_splits, r_row_kb0, r_panels, r_pos, r_freq, r_ndelta,
-      r_nlse2, r_kv_part;
+  size_t r_seg, r_seg_hi, r_dq_items, r_dq_kt, r_kv_items, r_kv_parts, r_kv_splits, r_row_kb0, r_panels, r_pos, r_freq,
+      r_ndelta, r_nlse2, r_kv_sums;
   size_t r_ds = 0;
-  size_t lean_total = 0;
   CastRegions cast;
+
+  size_t lean_needed() const { return lean_total[0]; }
+  size_t lean_wanted() const { return lean_total[1]; }
+  size_t stored_wanted() const { return stored_total[1]; }
 };
 
-void plan_bwd(const Batch& bt, pp_dtype dtype, int hq, int hkv, int d, BwdPlan* p) {
-  build_qplan(bt, kDqBlockM, kDqBlockN, &p->dq);
-  build_kplan(bt, kBwdBlockN, hq / hkv, &p->kv);
-  split_kplan(hkv, &p->kv, &p->kv_splits, &p->kv_slots);
+void lay_out_bwd(const Batch& bt, pp_dtype dtype, int hq, int hkv, int d, bool cut, BwdPlan* p) {
+  p->use_cut = cut;
+  p->cast = CastRegions();
   p->lay = Layout();
   p->r_seg = p->lay.add((size_t)bt.sumT * 4);
   p->r_seg_hi = p->lay.add((size_t)bt.sumT * 4);
   p->r_dq_items = p->lay.add(p->dq.items.size() * sizeof(QTileItem));
   p->r_dq_kt = p->lay.add(p->dq.ktiles.size() * sizeof(KTileEntry));
-  p->r_kv_items = p->lay.add(p->kv.size() * sizeof(KTileItem));
-  p->r_kv_splits = p->lay.add(p->kv_splits.size() * sizeof(KTileSplit));
-  p->ds_tiles = build_ds_panels(bt, kBwdBlockN, &p->row_kb0, &p->panels);
+  p->r_kv_items = p->lay.add((cut ? p->cut.items : p->kv).size() * sizeof(KTileItem));
+  p->r_kv_parts = p->lay.add(cut ? p->cut.parts.size() * sizeof(KTilePart) : 0);
+  p->r_kv_splits = p->lay.add(cut ? p->cut.splits.size() * sizeof(KTileSplit) : 0);
   p->r_row_kb0 = p->lay.add(p->row_kb0.size() * 4);
   p->r_panels = p->lay.add(p->panels.size() * sizeof(DsPanel));
   p->r_pos = p->lay.add((size_t)bt.sumT * 4);
@@ -784,7 +804,7 @@ void plan_bwd(const Batch& bt, pp_dtype dtype, int hq, int hkv, int d, BwdPlan* 
   p->lay.meta_bytes = p->lay.total;
   p->r_ndelta = p->lay.add((size_t)hq * bt.sumT * 4);
   p->r_nlse2 = p->lay.add((size_t)hq * bt.sumT * 4);
-  p->r_kv_part = p->lay.add((size_t)p->kv_slots * hkv * 2 * kBwdBlockN * d * 4);
+  p->r_kv_sums = p->lay.add(cut ? (size_t)p->cut.slots * hkv * kv_part_bytes(d) : 0);
   if (dtype == PP_FP32) {
     p->cast.on = true;
     p->cast.q = p->lay.add((size_t)bt.sumT * hq * d * 2);
@@ -792,8 +812,31 @@ void plan_bwd(const Batch& bt, pp_dtype dtype, int hq, int hkv, int d, BwdPlan* 
     p->cast.v = p->lay.add((size_t)bt.sumT * hkv * d * 2);
     p->cast.dout = p->lay.add((size_t)bt.sumT * hq * d * 2);
   }
-  p->lean_total = p->lay.total;
+  p->lean_total[cut] = p->lay.total;
   if (p->ds_tiles >= 0) p->r_ds = p->lay.add((size_t)p->ds_tiles * hq * 2048);
+  p->stored_total[cut] = p->lay.total;
+}
+
+void plan_bwd(const Batch& bt, pp_dtype dtype, int hq, int hkv, int d, BwdPlan* p) {
+  build_qplan(bt, kDqBlockM, kDqBlockN, &p->dq);
+  build_kplan(bt, kBwdBlockN, &p->kv);
+  p->ds_tiles = build_ds_panels(bt, kBwdBlockN, &p->row_kb0, &p->panels);
+  split_kplan(p->kv, hq / hkv, hkv, &p->cut);
+  if (!p->cut.items.empty()) lay_out_bwd(bt, dtype, hq, hkv, d, true, p);
+  lay_out_bwd(bt, dtype, hq, hkv, d, false, p);
+  if (p->cut.items.empty()) {
+    p->lean_total[1] = p->lean_total[0];
+    p->stored_total[1] = p->stored_total[0];
+  }
+}
+
+// Fixes the mode and the layout for a workspace of at least lean_needed() bytes.
+void settle_bwd(const Batch& bt, pp_dtype dtype, int hq, int hkv, int d, size_t ws_bytes, BwdPlan* p) {
+  const bool sums_only = p->lean_total[1] >= p->stored_total[0] && ws_bytes >= p->lean_total[1] &&
+                         ws_bytes < p->stored_total[1];
+  p->store_ds = p->ds_tiles >= 0 && ws_bytes >= p->stored_total[0] && !sums_only;
+  if (!p->cut.items.empty() && ws_bytes >= (p->store_ds ? p->stored_total[1] : p->lean_total[1]))
+    lay_out_bwd(bt, dtype, hq, hkv, d, true, p);
 }
 
 // One workspace layout serves the log-prob forward and its backward: the
@@ -1047,7 +1090,7 @@ pp_status pp_workspace_size(const pp_pack_desc* desc, pp_dtype dtype, int hq, in
   if (bwd) {
     BwdPlan p;
     plan_bwd(bt, dtype, hq, hkv, head_dim, &p);
-    *bwd = p.lean_total;  // the recompute mode; pp_bwd_stored_ds_workspace_size for the other
+    *bwd = p.lean_wanted();  // the recompute mode; pp_bwd_stored_ds_workspace_size for the other
   }
   if (logprob) {
     if (vocab < 1) return fail(PP_ERR_INVALID_ARGUMENT, "vocab must be >= 1 for the logprob size");
@@ -1262,8 +1305,12 @@ void bwd_image(const Batch& bt, const BwdPlan& p, int head_dim, const double* ro
   fill_seg_hi(bt, (int32_t*)img.at(p.lay.regions[p.r_seg_hi]));
   img.put(p.lay.regions[p.r_dq_items], p.dq.items.data(), p.dq.items.size() * sizeof(QTileItem));
   img.put(p.lay.regions[p.r_dq_kt], p.dq.ktiles.data(), p.dq.ktiles.size() * sizeof(KTileEntry));
-  img.put(p.lay.regions[p.r_kv_items], p.kv.data(), p.kv.size() * sizeof(KTileItem));
-  img.put(p.lay.regions[p.r_kv_splits], p.kv_splits.data(), p.kv_splits.size() * sizeof(KTileSplit));
+  const std::vector<KTileItem>& kv = p.use_cut ? p.cut.items : p.kv;
+  img.put(p.lay.regions[p.r_kv_items], kv.data(), kv.size() * sizeof(KTileItem));
+  if (p.use_cut) {
+    img.put(p.lay.regions[p.r_kv_parts], p.cut.parts.data(), p.cut.parts.size() * sizeof(KTilePart));
+    img.put(p.lay.regions[p.r_kv_splits], p.cut.splits.data(), p.cut.splits.size() * sizeof(KTileSplit));
+  }
   img.put(p.lay.regions[p.r_row_kb0], p.row_kb0.data(), p.row_kb0.size() * 4);
   img.put(p.lay.regions[p.r_panels], p.panels.data(), p.panels.size() * sizeof(DsPanel));
   std::vector<int32_t> pos;
@@ -1280,8 +1327,8 @@ void bwd_image(const Batch& bt, const BwdPlan& p, int head_dim, const double* ro
 // pinned memory) copied there ahead of its kernels.
 pp_status bwd_launch(const BwdPlan& p, void* ws, int sumT, pp_dtype dtype, int hq, int hkv, int head_dim,
                      float scale, const void* q, const void* k, const void* v, const void* o,
-                     const float* lse, const void* dout, void* dq, void* dk, void* dv, bool rope, bool store_ds,
-                     hipStream_t s, const void* stage_src = nullptr, size_t stage_bytes = 0) {
+                     const float* lse, const void* dout, void* dq, void* dk, void* dv, bool rope, hipStream_t s,
+                     const void* stage_src = nullptr, size_t stage_bytes = 0) {
   hipError_t e;
   StageLaunch pre = stage_of(ws, stage_src, stage_bytes);
   const void* dout_bf = dout;
@@ -1317,10 +1364,11 @@ pp_status bwd_launch(const BwdPlan& p, void* ws, int sumT, pp_dtype dtype, int h
   a.dq_ktiles = (const KTileEntry*)at(ws, p.lay, p.r_dq_kt);
   a.n_dq_items = (int)p.dq.items.size();
   a.kv_items = (const KTileItem*)at(ws, p.lay, p.r_kv_items);
-  a.n_kv_items = (int)p.kv.size();
+  a.n_kv_items = (int)(p.use_cut ? p.cut.items : p.kv).size();
+  a.kv_parts = (const KTilePart*)at(ws, p.lay, p.r_kv_parts);
   a.kv_splits = (const KTileSplit*)at(ws, p.lay, p.r_kv_splits);
-  a.n_kv_splits = (int)p.kv_splits.size();
-  a.kv_part = (float*)at(ws, p.lay, p.r_kv_part);
+  a.n_kv_splits = p.use_cut ? (int)p.cut.splits.size() : 0;
+  a.kv_part = (float*)at(ws, p.lay, p.r_kv_sums);
   a.seg_lo = (const int32_t*)at(ws, p.lay, p.r_seg);
   a.seg_hi = (const int32_t*)at(ws, p.lay, p.r_seg_hi);
   a.hq = hq;
@@ -1334,7 +1382,7 @@ pp_status bwd_launch(const BwdPlan& p, void* ws, int sumT, pp_dtype dtype, int h
     a.pos = (const int32_t*)at(ws, p.lay, p.r_pos);
     a.inv_freq = (const double*)at(ws, p.lay, p.r_freq);
   }
-  if (store_ds) {
+  if (p.store_ds) {
     a.ds = (__bf16*)at(ws, p.lay, p.r_ds);
     a.row_kb0 = (const int32_t*)at(ws, p.lay, p.r_row_kb0);
     a.kb_panel = (const DsPanel*)at(ws, p.lay, p.r_panels);
@@ -1359,12 +1407,12 @@ pp_status attn_bwd_impl(const pp_pack_desc* desc, pp_dtype dtype, int hq, int hk
   if ((st = check_bwd_ptrs(bt.sumT, q, k, v, o, lse, dout, dq, dk, dv)) != PP_OK) return st;
   BwdPlan p;
   plan_bwd(bt, dtype, hq, hkv, head_dim, &p);
-  if (ws_bytes < p.lean_total)
+  if (ws_bytes < p.lean_needed())
     return fail(PP_ERR_WORKSPACE_TOO_SMALL,
-                "backward needs %zu workspace bytes (%zu with the stored dS), got %zu", p.lean_total,
-                p.lay.total, ws_bytes);
-  const bool store_ds = p.ds_tiles >= 0 && ws_bytes >= p.lay.total;
-  if (p.lean_total && !ws) return fail(PP_ERR_INVALID_ARGUMENT, "ws is NULL");
+                "backward needs %zu workspace bytes (%zu with its partial sums, %zu with the stored dS), got %zu",
+                p.lean_needed(), p.lean_wanted(), p.stored_wanted(), ws_bytes);
+  settle_bwd(bt, dtype, hq, hkv, head_dim, ws_bytes, &p);
+  if (p.lean_needed() && !ws) return fail(PP_ERR_INVALID_ARGUMENT, "ws is NULL");
   if (ws && !aligned256(ws)) return fail(PP_ERR_INVALID_ARGUMENT, "ws must be 256-byte aligned");
   if (bt.sumT == 0) return PP_OK;
   MetaImage img;
@@ -1373,7 +1421,7 @@ pp_status attn_bwd_impl(const pp_pack_desc* desc, pp_dtype dtype, int hq, int hk
   hipStream_t s = (hipStream_t)hip_stream;
   return stage_with(ws, img.buf.data(), img.buf.size(), s, [&](const void* dev_src) {
     return bwd_launch(p, ws, bt.sumT, dtype, hq, hkv, head_dim, scale, q, k, v, o, lse, dout, dq, dk, dv,
-                      rope_base != nullptr, store_ds, s, dev_src, img.buf.size());
+                      rope_base != nullptr, s, dev_src, img.buf.size());
   });
 }
 
@@ -1413,7 +1461,6 @@ struct pp_plan {
   pp::BwdPlan bwd;
   void* ws;        // caller's workspace: forward region first, backward at bwd_off
   size_t bwd_off;
-  bool store_ds;   // the workspace holds the backward's stored-dS region
 };
 
 namespace pp {
@@ -1450,7 +1497,7 @@ pp_status pp_plan_workspace_size(const pp_pack_desc* desc, pp_dtype dtype, int h
   pp_plan p{};
   pp_status st = plan_common(desc, dtype, hq, hkv, head_dim, nullptr, &bt, &p);
   if (st != PP_OK) return st;
-  *bytes = p.bwd_off + p.bwd.lean_total;
+  *bytes = p.bwd_off + p.bwd.lean_wanted();
   return PP_OK;
 }
 
@@ -1462,8 +1509,8 @@ pp_status pp_bwd_stored_ds_workspace_size(const pp_pack_desc* desc, pp_dtype dty
   if (st != PP_OK) return st;
   if (p.bwd.ds_tiles < 0)
     return fail(PP_ERR_UNSUPPORTED, "the stored dS of this batch does not fit 32-bit tile offsets");
-  if (bwd) *bwd = p.bwd.lay.total;
-  if (plan) *plan = p.bwd_off + p.bwd.lay.total;
+  if (bwd) *bwd = p.bwd.stored_wanted();
+  if (plan) *plan = p.bwd_off + p.bwd.stored_wanted();
   return PP_OK;
 }
 
@@ -1475,11 +1522,12 @@ pp_status pp_plan_create(const pp_pack_desc* desc, pp_dtype dtype, int hq, int h
   if (!p) return fail(PP_ERR_INVALID_ARGUMENT, "out of host memory for the plan");
   Batch bt;
   pp_status st = plan_common(desc, dtype, hq, hkv, head_dim, rope_base, &bt, p);
-  const size_t total = p->bwd_off + p->bwd.lay.total, lean = p->bwd_off + p->bwd.lean_total;
+  const size_t lean = st == PP_OK ? p->bwd_off + p->bwd.lean_needed() : 0;
   if (st == PP_OK && ws_bytes < lean)
-    st = fail(PP_ERR_WORKSPACE_TOO_SMALL, "the plan needs %zu workspace bytes (%zu with the stored dS), got %zu",
-              lean, total, ws_bytes);
-  p->store_ds = p->bwd.ds_tiles >= 0 && ws_bytes >= total;
+    st = fail(PP_ERR_WORKSPACE_TOO_SMALL,
+              "the plan needs %zu workspace bytes (%zu with its partial sums, %zu with the stored dS), got %zu", lean,
+              p->bwd_off + p->bwd.lean_wanted(), p->bwd_off + p->bwd.stored_wanted(), ws_bytes);
+  if (st == PP_OK) settle_bwd(bt, dtype, hq, hkv, head_dim, ws_bytes - p->bwd_off, &p->bwd);
   if (st == PP_OK && lean && !ws) st = fail(PP_ERR_INVALID_ARGUMENT, "ws is NULL");
   if (st == PP_OK && ws && !aligned256(ws)) st = fail(PP_ERR_INVALID_ARGUMENT, "ws must be 256-byte aligned");
   if (st == PP_OK && bt.sumT > 0) {
@@ -1528,7 +1576,7 @@ pp_status pp_attn_bwd_planned(const pp_plan* plan, float scale, const void* q, c
   if (plan->sumT == 0) return PP_OK;
   void* ws_b = static_cast<char*>(plan->ws) + plan->bwd_off;
   return bwd_launch(plan->bwd, ws_b, plan->sumT, plan->dtype, plan->hq, plan->hkv, plan->head_dim, scale, q, k, v, o,
-                    lse, dout, dq, dk, dv, plan->rope, plan->store_ds, (hipStream_t)hip_stream);
+                    lse, dout, dq, dk, dv, plan->rope, (hipStream_t)hip_stream);
 }
 
 pp_status pp_attn_fwd(const pp_pack_desc* desc, pp_dtype dtype, int hq, int hkv, int head_dim,

@@ -93,9 +93,10 @@ struct AttnBwdLaunch {
   int n_dq_items;
   const KTileItem* kv_items;
   int n_kv_items;
-  // key tiles whose (head, step) pairs are spread over several items, and the
-  // fp32 partial dK and dV of every (slot, kv-head): 2 * kBwdBlockN * head_dim
-  // floats each
+  // key tiles whose (head, step) pairs are spread over several items, the items'
+  // parts of them, and the fp32 partial dK and dV of every (slot, kv-head):
+  // 2 * kBwdBlockN * head_dim floats each
+  const KTilePart* kv_parts;
   const KTileSplit* kv_splits;
   int n_kv_splits;
   float* kv_part;

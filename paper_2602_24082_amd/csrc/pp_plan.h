@@ -67,6 +67,7 @@ constexpr int kDqBlockN = PP_DQ_BLOCK_N;    // keys per dQ k-tile (32 or 64)
 constexpr int kBwdBlockN = 128;             // keys per dK/dV workgroup (8 waves: 4 key blocks x 2)
 constexpr int kBwdBlockM = 64;              // queries per dK/dV inner step
 constexpr int kComputeUnits = 256;          // of an MI355X
+constexpr int kMaxKvParts = 3 * kComputeUnits;  // parts of cut key tiles x kv-heads of a batch, at most
 
 // An entry of a query tile's key-tile list: the tile's first key (row-relative)
 // and, per 32-query block w of the query tile, a 2-bit class of the block's
@@ -99,11 +100,10 @@ struct QTileItem {
   int32_t row;     // row index (diagnostics)
 };
 
-// One work item of the dK/dV pass: keys [k0, k_end) of a row, the query range
-// that sees them, and the run [n_begin, n_end) of the tile's (head, step) pairs
-// that the item walks -- steps of kBwdBlockM queries, head by head.  A tile cut
-// into several items has one partial-sum slot per item; a whole tile (slot -1)
-// writes its gradients itself.
+// One work item of the dK/dV pass: keys [k0, k_end) of a row and the query range
+// that sees them.  The item walks the tile's (head, step) pairs -- steps of
+// kBwdBlockM queries, head by head -- all of them and writes the tile's gradients
+// itself (part -1), or those of one part of a cut tile.
 struct KTileItem {
   int32_t tok0;
   int32_t k0;
@@ -112,9 +112,16 @@ struct KTileItem {
   int32_t q_begin;  // first query that sees a key of the tile
   int32_t q_end;    // one past the last such query
   int32_t row;
+  int32_t part;     // index of its KTilePart, or -1
+};
+
+// A part of a cut tile: the run [n_begin, n_end) of the tile's pairs, whose sums go
+// to partial-sum slot `slot`.
+struct KTilePart {
   int32_t n_begin;
   int32_t n_end;
   int32_t slot;
+  int32_t pad;
 };
 
 // A key tile cut into several items: its partial sums sit in `parts`
