@@ -19,6 +19,7 @@
 #include <mutex>
 #include <new>
 #include <string>
+#include <thread>
 #include <vector>
 
 #include "../../include/pp_attn.h"
@@ -600,7 +601,9 @@ struct StagingSlot {
   void* dev = nullptr;        // its device address (null: copies go through hipMemcpyAsync)
   size_t cap = 0;
   hipEvent_t done = nullptr;  // recorded on the copy's stream (its device's event)
-  bool pending = false;
+  bool claimed = false;       // a call is filling it and enqueueing its launches
+  bool pending = false;       // done is recorded
+  uint64_t used = 0;          // order of the slots' last claims
 };
 
 // One ring per device: an event belongs to the device that was current when it
@@ -608,9 +611,10 @@ struct StagingSlot {
 // are never shared between devices.  A slot outgrown by a larger image is kept
 // (in `retired`) rather than freed: a kernel has read it, and pinned memory is
 // only released at unload.
+constexpr int kStageSlots = 16;
 struct StagingRing {
-  StagingSlot slot[8];
-  int next = 0;
+  StagingSlot slot[kStageSlots];
+  uint64_t claims = 0;
   std::vector<void*> retired;
 };
 
@@ -634,6 +638,42 @@ struct StagingRelease {
   }
 } g_stage_release;
 
+// Claims a slot of the ring: the one claimed longest ago if its work is done, else one
+// never used, else any whose work is done, else the one claimed longest ago, whose
+// work the caller waits for (*wait).  A slot that another stream's long kernels hold is
+// passed over, and nobody waits with the ring locked.
+StagingSlot* claim_slot(StagingRing& ring, bool* wait) {
+  auto done = [](const StagingSlot& s) {
+    if (hipEventQuery(s.done) == hipSuccess) return true;
+    (void)hipGetLastError();  // not ready (or an error, which the wait will report)
+    return false;
+  };
+  for (;; std::this_thread::yield()) {  // all slots claimed by other threads: they are let go within their calls
+    std::lock_guard<std::mutex> lk(g_stage_mu);
+    StagingSlot *fresh = nullptr, *oldest = nullptr;
+    for (StagingSlot& s : ring.slot) {
+      if (s.claimed) continue;
+      if (s.pending) oldest = !oldest || s.used < oldest->used ? &s : oldest;
+      else if (!fresh) fresh = &s;
+    }
+    StagingSlot* s = oldest ? oldest : fresh;
+    if (!s) continue;
+    *wait = oldest && !done(*oldest);
+    if (*wait && fresh) s = fresh;
+    for (StagingSlot& other : ring.slot) {
+      if (!*wait || s == fresh) break;
+      if (&other != oldest && !other.claimed && done(other)) {
+        s = &other;
+        *wait = false;
+      }
+    }
+    if (s == fresh) *wait = false;
+    s->claimed = true;
+    s->used = ++ring.claims;
+    return s;
+  }
+}
+
 // Stages `bytes` from `src` for device memory `dst` (on the current device,
 // whose stream `stream` is) through a pinned slot of that device's ring, then
 // calls `launch(dev_src)`, which enqueues the work that needs the data: with a
@@ -649,21 +689,34 @@ pp_status stage_with(void* dst, const void* src, size_t bytes, hipStream_t strea
   int dev = 0;
   hipError_t e = hipGetDevice(&dev);
   if (e != hipSuccess) return hip_fail(e, "hipGetDevice(staging)");
-  std::lock_guard<std::mutex> lk(g_stage_mu);
-  StagingRing& ring = g_stage[dev];
-  StagingSlot& s = ring.slot[ring.next];
-  ring.next = (ring.next + 1) % 8;
-  if (s.pending) {
+  StagingRing* ring;
+  {
+    std::lock_guard<std::mutex> lk(g_stage_mu);
+    ring = &g_stage[dev];
+  }
+  bool wait = false;
+  StagingSlot& s = *claim_slot(*ring, &wait);
+  struct Release {
+    StagingSlot& s;
+    ~Release() {
+      std::lock_guard<std::mutex> lk(g_stage_mu);
+      s.claimed = false;
+    }
+  } release{s};
+  if (wait) {
     e = hipEventSynchronize(s.done);
     if (e != hipSuccess) return hip_fail(e, "hipEventSynchronize(staging)");
-    s.pending = false;
   }
+  s.pending = false;
   if (!s.done) {
     e = hipEventCreateWithFlags(&s.done, hipEventDisableTiming);
     if (e != hipSuccess) return hip_fail(e, "hipEventCreate(staging)");
   }
   if (s.cap < bytes) {
-    if (s.host) ring.retired.push_back(s.host);
+    if (s.host) {
+      std::lock_guard<std::mutex> lk(g_stage_mu);
+      ring->retired.push_back(s.host);
+    }
     s.host = s.dev = nullptr;
     s.cap = 0;
     size_t cap = std::max<size_t>(bytes, 1 << 20);
