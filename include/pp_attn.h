@@ -444,7 +444,12 @@ pp_status pp_timing_enable(int on);
 /* Restricts timing to the launches named in `names`, a comma-separated list of
  * the names pp_timing_get reports (e.g. "pp_logprob_rows,pp_attn_fwd"); NULL or
  * "" times every launch again.  The list is copied.  Launches left out get no
- * events, so the work around them runs as it would untimed. */
+ * events, so the work around them runs as it would untimed.
+ * A launch that does several jobs is one entry: what precedes a call's kernels is
+ * "pp_stage" with a metadata copy, else "pp_to_bf16" (conversions of fp32 inputs)
+ * or "pp_fill_zero" (zeros of the per-token log-probs), and the reward head's
+ * backward "pp_rm_dhidden".  Selected by the name of another of its jobs (one of
+ * those, "pp_rm_dw"), it is timed, whole, under that name. */
 pp_status pp_timing_select(const char* names);
 pp_status pp_timing_reset(void);
 int pp_timing_count(void);

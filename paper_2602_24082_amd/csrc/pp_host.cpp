@@ -1066,10 +1066,12 @@ pp_status report_error(pp_status st, const char* fmt, ...) {
 
 pp_status report_hip_error(hipError_t e, const char* what) { return hip_fail(e, what); }
 
-TimingScope::TimingScope(const char* name, hipStream_t stream) : name_(name), stream_(stream) {
+TimingScope::TimingScope(std::initializer_list<const char*> names, hipStream_t stream) : stream_(stream) {
   if (!g_time_on.load(std::memory_order_relaxed)) return;
   std::lock_guard<std::mutex> lk(g_time_mu);
-  if (!timing_selected_locked(name)) return;
+  for (const char* name : names)
+    if (!name_ && name && timing_selected_locked(name)) name_ = name;
+  if (!name_) return;
   hipEvent_t a = pool_get(), b = pool_get();
   if (!a || !b || hipEventRecord(a, stream) != hipSuccess) {
     (void)hipGetLastError();

@@ -6,6 +6,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <initializer_list>
+
 #include "../../include/pp_attn.h"
 #include "pp_plan.h"
 
@@ -17,13 +19,16 @@ enum ElemType { kBF16 = 0, kFP32 = 1 };
 // The scope owns its two events until its destructor has recorded the second;
 // only then does the launch join the list that pp_timing_get drains, so a
 // drain from another thread never sees a half-recorded launch.
+// A launch that does several jobs has a name for each (null: not in this launch): it is
+// timed as the first, or as the first that pp_timing_select asks for.
 struct TimingScope {
-  TimingScope(const char* name, hipStream_t stream);
+  TimingScope(const char* name, hipStream_t stream) : TimingScope({name}, stream) {}
+  TimingScope(std::initializer_list<const char*> names, hipStream_t stream);
   ~TimingScope();
   TimingScope(const TimingScope&) = delete;
   TimingScope& operator=(const TimingScope&) = delete;
  private:
-  const char* name_;
+  const char* name_ = nullptr;
   hipStream_t stream_;
   hipEvent_t start_ = nullptr;
   hipEvent_t stop_ = nullptr;

@@ -172,7 +172,7 @@ hipError_t launch_rm_scores(const RmLaunch& a, hipStream_t s) {
 }
 
 hipError_t launch_rm_bwd(const RmBwdLaunch& a, hipStream_t s) {
-  TimingScope t("pp_rm_dhidden", s);
+  TimingScope t({"pp_rm_dhidden", "pp_rm_dw"}, s);
   const int dw_blocks = (a.H + kRmThreads - 1) / kRmThreads;
   const dim3 grid((unsigned)(dw_blocks + 1 + a.sumT));
   if (a.dtype == kBF16)

@@ -74,7 +74,9 @@ hipError_t launch_stage(const StageLaunch& a, hipStream_t s) {
   for (int c = 0; c < kStageCasts; ++c) total += nb.cast[c] = blocks((a.cast[c].n + 3) / 4);
   total += nb.zero = blocks(a.n_zero);
   if (total == 0) return hipSuccess;
-  TimingScope t(nb.copy ? "pp_stage" : "pp_to_bf16", s);
+  int64_t casts = 0;
+  for (int n : nb.cast) casts += n;
+  TimingScope t({nb.copy ? "pp_stage" : nullptr, casts ? "pp_to_bf16" : nullptr, nb.zero ? "pp_fill_zero" : nullptr}, s);
   hipLaunchKernelGGL(stage_kernel, dim3((unsigned)total), dim3(kThreads), 0, s, a, nb);
   return hipGetLastError();
 }
