@@ -514,13 +514,22 @@ __device__ __forceinline__ float sigmoid_f(float x) {
   return e / (1.f + e);
 }
 
-// Rows of 3 to this many slots have their pairs spread over the threads.
+// Rows of 3 to kLossPairsResp slots have their pairs spread over the threads, in batches
+// of up to kLossSpreadRows rows.
 constexpr int kLossPairsResp = 8;
+constexpr int kLossSpreadRows = 64;
 
 // SPREAD: a thread a pair forms its softplus and sigmoid, then a thread a row and a
 // thread a slot add them in the order of the plain form below, a thread a row,
 // whose chain of pairs sets the time (8 rows of 4 ranked responses: 6.6 us plain,
 // 4.1 us spread).  With two slots there is no chain: 3.5 us plain, 4.0 us spread.
+// A turn takes 256 / pairs rows (9 at 8 slots) where the plain form takes 256, so that
+// wins in larger batches.  Timed with the events' 3 us, plain / spread in us:
+//   slots     8 rows     64 rows    128 rows    2048 rows
+//     3     7.3 / 6.2   7.0 / 6.4   7.3 / 8.2    26 / 49
+//     4     9.2 / 6.4   9.6 / 8.7   9.6 / 12.3   45 / 99
+//     6    14.8 / 6.5  14.2 / 13.4 15.1 / 22.4   94 / 273
+//     8    23.1 / 7.0  25.4 / 24.6 25.9 / 42.1  202 / 570
 template <bool SPREAD>
 __global__ __launch_bounds__(256) void pair_loss_kernel(LossLaunch a) {
   const int tid = threadIdx.x;
@@ -675,7 +684,7 @@ hipError_t launch_logprob_bwd(const LogprobBwdLaunch& a, hipStream_t s) {
 
 hipError_t launch_loss(const LossLaunch& a, hipStream_t s) {
   TimingScope t("pp_pair_loss", s);
-  if (a.K_max >= 3 && a.K_max <= kLossPairsResp)
+  if (a.K_max >= 3 && a.K_max <= kLossPairsResp && a.B <= kLossSpreadRows)
     hipLaunchKernelGGL(pair_loss_kernel<true>, dim3(1), dim3(256), 0, s, a);
   else
     hipLaunchKernelGGL(pair_loss_kernel<false>, dim3(1), dim3(256), 0, s, a);
