@@ -309,31 +309,55 @@ void build_kplan(const Batch& bt, int BN, std::vector<KTileItem>* out) {
 // Parts of a tile of n (head, step) pairs when no part may exceed `most`.
 inline int split_parts(int n, int most) { return most > 0 && n > most ? (n + most - 1) / most : 1; }
 
-// Finish time, in steps, of one kv-head's items (longest first, each tile cut
-// so that no part exceeds `most` steps; 0: none) on `units` compute units that
-// each take the next item when they are free, and the parts of cut tiles.
-double kplan_span(const std::vector<KTileItem>& tiles, int G, int most, int units, int* n_parts) {
+// Finish time, in steps, of one kv-head's items (longest first, each tile of `pairs`
+// pairs cut so that no part exceeds `most`; 0: none) on `units` compute units that
+// each take the next item when they are free, plus `extra` for every part of a cut
+// tile; *n_parts: those parts.  A bound at least `enough` is returned as it is.
+struct KPlanSpan {
   // in steps of kBwdBlockM queries (2.0 us at head size 128, measured on 8B-shaped rows): 1.6 for a workgroup's K/V
   // load and epilogue, 1 more to write a part's fp32 sums
-  constexpr double kItem = 1.6, kPart = 1.0;
-  std::vector<std::pair<int, bool>> items;  // steps, part of a cut tile
-  *n_parts = 0;
-  for (const KTileItem& t : tiles) {
-    const int n = tile_pairs(t, G), parts = split_parts(n, most);
-    if (parts > 1) *n_parts += parts;
-    for (int i = 0; i < parts; ++i) items.emplace_back((int)((int64_t)n * (i + 1) / parts - (int64_t)n * i / parts), parts > 1);
+  static constexpr double kItem = 1.6, kPart = 1.0;
+  static double cost(int key) { return (key >> 1) + kItem + (key & 1 ? kPart : 0.0); }
+
+  std::vector<int> keys;     // 2 x pairs + part of a cut tile
+  std::vector<double> busy;  // min-heap of the units' finish times
+
+  double operator()(const std::vector<int>& pairs, int most, int units, double extra, double enough, int* n_parts) {
+    keys.clear();
+    *n_parts = 0;
+    int64_t sum = 0;
+    for (int n : pairs) {
+      const int parts = split_parts(n, most);
+      if (parts > 1) *n_parts += parts;
+      for (int i = 0; i < parts; ++i)
+        keys.push_back((int)((int64_t)n * (i + 1) / parts - (int64_t)n * i / parts) * 2 + (parts > 1));
+      sum += n;
+    }
+    const double more = extra * *n_parts;
+    const double least = ((double)sum + kItem * (double)keys.size() + kPart * *n_parts) / units + more;
+    if (least >= enough) return least;
+    std::sort(keys.begin(), keys.end(), std::greater<int>());
+    const size_t n = keys.size(), first = std::min(n, (size_t)units);
+    double span = 0;
+    busy.resize(first);
+    for (size_t i = 0; i < first; ++i) span = std::max(span, busy[i] = cost(keys[i]));
+    if (n > first) std::make_heap(busy.begin(), busy.end(), std::greater<double>());
+    for (size_t i = first; i < n; ++i) {
+      // the unit that is free first takes the item: its new time sinks from the top
+      const double t = busy[0] + cost(keys[i]);
+      span = std::max(span, t);
+      size_t at = 0;
+      for (size_t c = 1; c < first; c = 2 * at + 1) {
+        if (c + 1 < first && busy[c + 1] < busy[c]) ++c;
+        if (busy[c] >= t) break;
+        busy[at] = busy[c];
+        at = c;
+      }
+      busy[at] = t;
+    }
+    return span + more;
   }
-  std::stable_sort(items.begin(), items.end(), [](const auto& a, const auto& b) { return a.first > b.first; });
-  std::vector<double> busy(units, 0.0);  // min-heap of the units' finish times
-  double span = 0;
-  for (const auto& it : items) {
-    std::pop_heap(busy.begin(), busy.end(), std::greater<double>());
-    busy.back() += it.first + kItem + (it.second ? kPart : 0.0);
-    span = std::max(span, busy.back());
-    std::push_heap(busy.begin(), busy.end(), std::greater<double>());
-  }
-  return span;
-}
+};
 
 // The dK/dV pass's items with the longest key tiles cut.
 struct KvCut {
@@ -366,41 +390,52 @@ void split_kplan(const std::vector<KTileItem>& kv, int G, int hkv, KvCut* cut) {
   *cut = KvCut();
   if (kv.empty() || (int64_t)kv.size() * hkv > 2 * kComputeUnits) return;
   const int units = std::max(1, kComputeUnits / hkv);
+  std::vector<int> pairs;
   int64_t work = 0;
-  for (const KTileItem& t : kv) work += tile_pairs(t, G);
-  const int even = (int)((work + units - 1) / units), longest = tile_pairs(kv[0], G);
+  for (const KTileItem& t : kv) {
+    pairs.push_back(tile_pairs(t, G));
+    work += pairs.back();
+  }
+  const int even = (int)((work + units - 1) / units), longest = pairs[0];
   if (longest < 8 || longest <= even) return;  // the units' even share is the longer
   int parts = 0;
-  const double whole = kplan_span(kv, G, 0, units, &parts);
+  KPlanSpan span_of;
+  const double whole = span_of(pairs, 0, units, 0.0, HUGE_VAL, &parts);
   double best = whole;
   int most = 0;
   for (int sixths : {9, 6, 4, 3, 2}) {
     const int m = std::max(4, (even * sixths + 5) / 6);
-    const double span = kplan_span(kv, G, m, units, &parts) + kLaunch + (double)parts * hkv / kPartsPerStep;
+    const double span = kLaunch + span_of(pairs, m, units, hkv / kPartsPerStep, best - kLaunch, &parts);
     if (span < best && (int64_t)parts * hkv <= kMaxKvParts) {
       best = span;
       most = m;
     }
   }
   if (most == 0 || best > 0.9 * whole) return;
-  std::vector<std::pair<int, KTileItem>> items;  // pairs, item
-  for (const KTileItem& t : kv) {
-    const int n = tile_pairs(t, G), k = split_parts(n, most);
+  struct Run {
+    int pairs, tile, part;
+  };
+  std::vector<Run> runs;
+  for (size_t j = 0; j < kv.size(); ++j) {
+    const KTileItem& t = kv[j];
+    const int n = pairs[j], k = split_parts(n, most);
     if (k == 1) {
-      items.emplace_back(n, t);
+      runs.push_back({n, (int)j, -1});
       continue;
     }
     cut->splits.push_back(KTileSplit{t.tok0, t.k0, t.k_end, cut->slots, k, 0});
     for (int i = 0; i < k; ++i) {
       const KTilePart p{(int32_t)((int64_t)n * i / k), (int32_t)((int64_t)n * (i + 1) / k), cut->slots++, 0};
-      KTileItem it = t;
-      it.part = (int32_t)cut->parts.size();
+      runs.push_back({p.n_end - p.n_begin, (int)j, (int)cut->parts.size()});
       cut->parts.push_back(p);
-      items.emplace_back(p.n_end - p.n_begin, it);
     }
   }
-  std::stable_sort(items.begin(), items.end(), [](const auto& a, const auto& b) { return a.first > b.first; });
-  for (const auto& it : items) cut->items.push_back(it.second);
+  std::stable_sort(runs.begin(), runs.end(), [](const Run& a, const Run& b) { return a.pairs > b.pairs; });
+  cut->items.reserve(runs.size());
+  for (const Run& r : runs) {
+    cut->items.push_back(kv[r.tile]);
+    cut->items.back().part = r.part;
+  }
 }
 
 // The per-token arrays below are filled segment by segment: a validated row is
@@ -582,6 +617,7 @@ struct Layout {
   std::vector<Region> regions;
   size_t meta_bytes = 0;   // host-staged prefix
   size_t total = 0;
+  Layout() { regions.reserve(24); }
   size_t add(size_t bytes) {
     Region r;
     r.off = total;
