@@ -314,8 +314,8 @@ inline int split_parts(int n, int most) { return most > 0 && n > most ? (n + mos
 // each take the next item when they are free, plus `extra` for every part of a cut
 // tile; *n_parts: those parts.  A bound at least `enough` is returned as it is.
 struct KPlanSpan {
-  // in steps of kBwdBlockM queries (2.0 us at head size 128, measured on 8B-shaped rows): 1.6 for a workgroup's K/V
-  // load and epilogue, 1 more to write a part's fp32 sums
+  // in steps of kBwdBlockM queries (2.0 us at head size 128 with all units busy, 1.5 with few; 1.05 at 64): 1.6 for a
+  // workgroup's K/V load and epilogue, 1 more to write a part's fp32 sums
   static constexpr double kItem = 1.6, kPart = 1.0;
   static double cost(int key) { return (key >> 1) + kItem + (key & 1 ? kPart : 0.0); }
 
@@ -378,11 +378,17 @@ inline size_t kv_part_bytes(int d) { return (size_t)2 * kBwdBlockN * d * 4; }
 // in the parts' fixed work than it evens out (measured 0 to 14% slower).  The
 // longest part allowed is the one of five that gives the smallest estimate: from
 // half as much again as the units' even share, which few tiles exceed, to a third
-// of it.  The estimate counts the launch that adds the partial sums and their
-// bytes at the 3 TB/s that launch reaches (46 parts of one kv-head a step).  A cut
-// has to shorten it by a tenth.  On that row the pass took 201 us whole and takes
-// 89 us cut (53 parts), plus 10 to 15 us for the sums; a rule of even shares, halves
-// and thirds of them took 101 us (67 parts).  One row of 4200 tokens: 324 -> 298 us.
+// of it.  The estimate charges the launch that adds the partial sums 2.5 steps and
+// every 46 parts of one kv-head a step more.  That is about twice what the launch
+// itself takes for its bytes (400 parts, 52 MB, in 11 us; 432 after 4200 tokens in
+// 16), for both head sizes: it stands for all that a further part costs.  A cut has
+// to shorten the estimate by a tenth.
+//
+// On that row the pass took 201 us whole and takes 90 us cut (50 parts of each
+// kv-head) and 11 us for the sums; one row of 4200 tokens 417 -> 280 and 16.  Of 60
+// batches (1 to 24 rows, 320 to 21600 tokens, three head layouts at each head size),
+// each timed whole and at seven cuts from four times the even share to a third, the
+// rule's choice was the fastest in 56 and within 1.2% of it in all.
 //
 // Cuts into more than kMaxKvParts parts (96 MiB of sums at head size 128) are left out.
 void split_kplan(const std::vector<KTileItem>& kv, int G, int hkv, KvCut* cut) {
