@@ -54,6 +54,31 @@ struct StageLaunch {
 };
 hipError_t launch_stage(const StageLaunch& a, hipStream_t s);
 
+// Blocks of kStageThreads threads of that launch: the copy's first, then each
+// conversion's, then the zeros'.  A launch holds fewer than 2^32 threads in all, and the
+// conversions of a large fp32 batch may be more vectors than that together, so each
+// has at most kStageCastBlocks blocks, which walk its vectors in strides.
+constexpr int kStageThreads = 256;
+constexpr int64_t kStageCastBlocks = 1 << 20;
+struct StageBlocks {
+  int copy;
+  int cast[kStageCasts];
+  int zero;
+  int64_t total;
+};
+inline StageBlocks stage_blocks(const StageLaunch& a) {
+  auto blocks = [](int64_t threads) { return (threads + kStageThreads - 1) / kStageThreads; };
+  const int64_t n16 = (int64_t)(a.bytes / 16), tail = (int64_t)(a.bytes % 16);
+  StageBlocks nb{};
+  nb.total = nb.copy = (int)blocks(n16 > tail ? n16 : tail);
+  for (int c = 0; c < kStageCasts; ++c) {
+    const int64_t n = blocks((a.cast[c].n + 3) / 4);
+    nb.total += nb.cast[c] = (int)(n < kStageCastBlocks ? n : kStageCastBlocks);
+  }
+  nb.total += nb.zero = (int)blocks(a.n_zero);
+  return nb;
+}
+
 // q, k, v are bf16; o has dtype `dtype`.
 struct AttnFwdLaunch {
   const void* q;

@@ -19,14 +19,7 @@ namespace {
 
 typedef uint32_t Chunk16 __attribute__((ext_vector_type(4)));
 
-constexpr int kThreads = 256;
-
-// Work of the launch's blocks: the copy's first, then each conversion's, then the zeros'.
-struct StageBlocks {
-  int copy;
-  int cast[kStageCasts];
-  int zero;
-};
+constexpr int kThreads = kStageThreads;
 
 __global__ __launch_bounds__(kThreads) void stage_kernel(StageLaunch a, StageBlocks nb) {
   int b = blockIdx.x;
@@ -48,12 +41,13 @@ __global__ __launch_bounds__(kThreads) void stage_kernel(StageLaunch a, StageBlo
       const float* src = a.cast[c].src;
       __bf16* dst = static_cast<__bf16*>(a.cast[c].dst);
       const int64_t n = a.cast[c].n;
-      const int64_t i = ((int64_t)b * kThreads + threadIdx.x) * 4;
-      if (i + 4 <= n) {
-        const f32x4 v = *reinterpret_cast<const f32x4*>(src + i);
-        *reinterpret_cast<bf16x4*>(dst + i) = __builtin_convertvector(v, bf16x4);
-      } else {
-        for (int64_t j = i; j < n; ++j) dst[j] = (__bf16)src[j];
+      for (int64_t i = ((int64_t)b * kThreads + threadIdx.x) * 4; i < n; i += (int64_t)nb.cast[c] * kThreads * 4) {
+        if (i + 4 <= n) {
+          const f32x4 v = *reinterpret_cast<const f32x4*>(src + i);
+          *reinterpret_cast<bf16x4*>(dst + i) = __builtin_convertvector(v, bf16x4);
+        } else {
+          for (int64_t j = i; j < n; ++j) dst[j] = (__bf16)src[j];
+        }
       }
       return;
     }
@@ -66,18 +60,12 @@ __global__ __launch_bounds__(kThreads) void stage_kernel(StageLaunch a, StageBlo
 }  // namespace
 
 hipError_t launch_stage(const StageLaunch& a, hipStream_t s) {
-  auto blocks = [](int64_t threads) { return (int)((threads + kThreads - 1) / kThreads); };
-  const int64_t n16 = (int64_t)(a.bytes / 16), tail = (int64_t)(a.bytes % 16);
-  StageBlocks nb{};
-  nb.copy = blocks(n16 > tail ? n16 : tail);
-  int64_t total = nb.copy;
-  for (int c = 0; c < kStageCasts; ++c) total += nb.cast[c] = blocks((a.cast[c].n + 3) / 4);
-  total += nb.zero = blocks(a.n_zero);
-  if (total == 0) return hipSuccess;
+  const StageBlocks nb = stage_blocks(a);
+  if (nb.total == 0) return hipSuccess;
   int64_t casts = 0;
   for (int n : nb.cast) casts += n;
   TimingScope t({nb.copy ? "pp_stage" : nullptr, casts ? "pp_to_bf16" : nullptr, nb.zero ? "pp_fill_zero" : nullptr}, s);
-  hipLaunchKernelGGL(stage_kernel, dim3((unsigned)total), dim3(kThreads), 0, s, a, nb);
+  hipLaunchKernelGGL(stage_kernel, dim3((unsigned)nb.total), dim3(kThreads), 0, s, a, nb);
   return hipGetLastError();
 }
 
