@@ -156,7 +156,8 @@ __global__ __launch_bounds__(kRmThreads) void rm_bwd_kernel(RmBwdLaunch a, int d
   const int b = blockIdx.x;
   if (b < dw_blocks) rm_dw_columns<T>(a, b);
   else if (b == dw_blocks) rm_dbias(a);
-  else rm_dhidden_row<T>(a, b - dw_blocks - 1);
+  else
+    for (int64_t r = b - dw_blocks - 1; r < a.sumT; r += gridDim.x - dw_blocks - 1) rm_dhidden_row<T>(a, r);
 }
 
 }  // namespace
@@ -174,7 +175,9 @@ hipError_t launch_rm_scores(const RmLaunch& a, hipStream_t s) {
 hipError_t launch_rm_bwd(const RmBwdLaunch& a, hipStream_t s) {
   TimingScope t({"pp_rm_dhidden", "pp_rm_dw"}, s);
   const int dw_blocks = (a.H + kRmThreads - 1) / kRmThreads;
-  const dim3 grid((unsigned)(dw_blocks + 1 + a.sumT));
+  // a workgroup a row as far as a launch's 2^32 - 1 threads go
+  const int64_t most = 0xffffffffll / kRmThreads - dw_blocks - 1;
+  const dim3 grid((unsigned)(dw_blocks + 1 + (a.sumT < most ? a.sumT : most)));
   if (a.dtype == kBF16)
     hipLaunchKernelGGL(rm_bwd_kernel<__bf16>, grid, dim3(kRmThreads), 0, s, a, dw_blocks);
   else
