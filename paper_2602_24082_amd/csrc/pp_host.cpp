@@ -955,16 +955,16 @@ void plan_logprob(const Batch& bt, LogprobPlan* p) {
   p->r_tok = p->lay.add((size_t)bt.sumT * 4);
 }
 
-// The forward's metadata, or the backward's (label slots; dense: each row's record).
+// The forward's metadata (response records), or the backward's (label slots; dense: each row's record).
 void logprob_image(const Batch& bt, const LogprobPlan& p, bool bwd, bool dense, MetaImage* img) {
   const auto& reg = p.lay.regions;
   img->buf.reserve(p.lay.meta_bytes);
   // the last region first: the image has its size before the places are taken
   if (dense) img->at(reg[p.r_row_item]);
   if (bwd) img->at(reg[p.r_label_out]);
-  img->at(reg[p.r_resp]);
+  else img->at(reg[p.r_resp]);
   fill_lplan(bt, (LogitRowItem*)img->at(reg[p.r_rows]), (int32_t*)img->at(reg[p.r_labels]),
-             (RespItem*)img->at(reg[p.r_resp]), bwd ? (int32_t*)img->at(reg[p.r_label_out]) : nullptr,
+             bwd ? nullptr : (RespItem*)img->at(reg[p.r_resp]), bwd ? (int32_t*)img->at(reg[p.r_label_out]) : nullptr,
              dense ? (int32_t*)img->at(reg[p.r_row_item]) : nullptr);
 }
 
@@ -1794,7 +1794,6 @@ pp_status pp_seq_logprob(const pp_pack_desc* desc, pp_dtype logits_dtype, int vo
   a.n_rows = (int)p.n.rows;
   a.n_resp = (int)p.n.resp;
   a.vocab = vocab;
-  a.sumT = bt.sumT;
   a.dtype = logits_dtype == PP_FP32 ? kFP32 : kBF16;
   return stage_with(ws, img.buf.data(), img.buf.size(), s, [&](const void* dev_src) -> pp_status {
     StageLaunch pre = stage_of(ws, dev_src, img.buf.size());

@@ -175,7 +175,6 @@ struct LogprobLaunch {
   int n_rows;
   int n_resp;
   int vocab;
-  int sumT;
   int dtype;
 };
 hipError_t launch_logprob(const LogprobLaunch& a, hipStream_t s);
