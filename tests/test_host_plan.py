@@ -1,7 +1,8 @@
-"""CPU tests of the planner's shortcuts against the dense mask: the key tiles listed for
-every 128-query tile (a tile in full view, or far from the tile's own responses, is
-settled without counting pairs), the 32 x 32 blocks of dS the stored mode keeps, and the
-log-prob records, each through the workspace sizes they make."""
+"""CPU tests of the workspace sizes that the planner's shortcuts make, against the dense
+mask: how many key tiles are listed for all 128-query tiles (a tile in full view, or far
+from the tile's own responses, is settled without counting pairs), how many 32 x 32 blocks
+of dS the stored mode keeps, and how many log-prob records there are.  Sizes are rounded
+to 256 bytes; test_host_plan_records.py holds the records themselves, entry by entry."""
 import numpy as np
 import pytest
 
