@@ -18,18 +18,21 @@
 //                (at head size 64 dP accumulates from -delta_i)
 //                dV^T += dO^T P,  dK^T += Q^T dS   (dO^T, Q^T by transposed LDS reads)
 //
-//   stored dS (the default; the workspace holds one bf16 dS value per pair of
+//   stored dS (a workspace with room for one bf16 dS value per pair of
 //              every 32 x 32 block with a visible pair, per head):
 //                bwd_prep   delta_i = dO_i . O_i and -lse_i log2(e)
 //                bwd_dkdv   as above, and each wave stores its 32 x 32 dS block
 //                bwd_dq_ds  query-major: dQ^T += K^T dS^T from the stored blocks,
 //                           no recomputation of S, P or dP
-//   recompute (a workspace without the dS region: scratch linear in tokens):
+//   recompute (the default: a workspace without that room):
 //                bwd_dq     query-major, first: its prologue forms delta and
 //                           -lse log2(e) for its queries and stores them for
 //                           dK/dV; then S^T = K Q^T, dP^T = V dO^T,
 //                           dS^T = P^T (dP^T - delta), dQ^T += K^T dS^T
 //                bwd_dkdv   as above
+//
+//   In either mode the key tiles of a batch that leaves compute units idle may be
+//   cut into several work items of bwd_dkdv, whose fp32 sums bwd_kv_combine adds.
 //
 // All products run on v_mfma_f32_32x32x16_bf16 with fp32 accumulation.  Q, K, V
 // and dO are bf16 here (fp32 callers are converted by a pre-pass); O and the
