@@ -186,7 +186,11 @@ struct DkdvSmem {
 // the values its dK product uses) as one 2 KB tile: key row ln of the tile
 // holds the lane pair's two accumulator halves side by side (64-byte rows,
 // column c = query ds_query_of_column(c) of the block).
-template <int D, typename TO, bool ROPE, bool STORE_DS>
+//
+// CUT: the items may be parts of cut tiles.  A kernel of its own, so that whole tiles
+// pay nothing for it: with both in one, the rotary epilogue spilled and the pass took
+// 1% longer on the 8B-shaped batch (384 -> 389 us).
+template <int D, typename TO, bool ROPE, bool STORE_DS, bool CUT>
 __global__ __launch_bounds__(512, 1) void bwd_dkdv_kernel(BwdParams<TO> p) {
   using Dma = TileDma<D, KBM / 8>;
   using KvDma = TileDma<D, KBN / 8>;
@@ -227,7 +231,7 @@ __global__ __launch_bounds__(512, 1) void bwd_dkdv_kernel(BwdParams<TO> p) {
   const int nsteps = (nq + KBM - 1) / KBM;
   // the pairs this item walks, and the slot of its sums (-1: the whole tile)
   int n_first = 0, n_iter = G * nsteps, slot = -1;
-  if (it.part >= 0) {
+  if (CUT && it.part >= 0) {
     const KTilePart pt = load_uniform(p.kv_parts + it.part);
     n_first = pt.n_begin;
     n_iter = pt.n_end;
@@ -254,7 +258,7 @@ __global__ __launch_bounds__(512, 1) void bwd_dkdv_kernel(BwdParams<TO> p) {
   Dma dma;
   dma.init(wave * (KBM / 8), q_stride, lane);
   int f_hh = 0, f_stp = 0;  // next step to fetch
-  if (n_first > 0) {
+  if (CUT && n_first > 0) {
     f_hh = n_first / nsteps;
     f_stp = n_first - f_hh * nsteps;
   }
@@ -428,7 +432,7 @@ __global__ __launch_bounds__(512, 1) void bwd_dkdv_kernel(BwdParams<TO> p) {
   wait_vmem<0>();  // a tile of padding keys has no steps: its K/V DMA is still owed
   // add the second query half's partials into the first half's waves: first dK, then dV
   float* red = sm.red[kb];
-  if (slot >= 0) {
+  if (CUT && slot >= 0) {
     // a part of a cut tile: the sums go out as they lie in the accumulators
 #pragma unroll
     for (int pass = 0; pass < 2; ++pass) {
@@ -934,6 +938,18 @@ __global__ __launch_bounds__(NW * 64, PP_DQ_MIN_WAVES) void bwd_dq_ds_kernel(Bwd
                  f32x4{acc[m][4 * r4], acc[m][4 * r4 + 1], acc[m][4 * r4 + 2], acc[m][4 * r4 + 3]});
 }
 
+template <int D, typename TO, bool STORE_DS>
+void launch_dkdv(const AttnBwdLaunch& a, const BwdParams<TO>& p, dim3 grid, hipStream_t s) {
+  auto launch = [&](auto kernel) { hipLaunchKernelGGL(kernel, grid, dim3(512), 0, s, p); };
+  if (a.n_kv_splits > 0) {
+    if (a.rope) launch(bwd_dkdv_kernel<D, TO, true, STORE_DS, true>);
+    else launch(bwd_dkdv_kernel<D, TO, false, STORE_DS, true>);
+  } else {
+    if (a.rope) launch(bwd_dkdv_kernel<D, TO, true, STORE_DS, false>);
+    else launch(bwd_dkdv_kernel<D, TO, false, STORE_DS, false>);
+  }
+}
+
 // The sums of the cut key tiles, if there are any.
 template <int D, typename TO>
 hipError_t launch_kv_combine(const AttnBwdLaunch& a, const BwdParams<TO>& p, hipStream_t s) {
@@ -993,8 +1009,7 @@ hipError_t launch_bwd_t(const AttnBwdLaunch& a, hipStream_t s) {
     {
       TimingScope t("pp_attn_bwd_dkdv", s);
       const dim3 grid((unsigned)((int64_t)a.n_kv_items * a.hkv));
-      if (a.rope) hipLaunchKernelGGL((bwd_dkdv_kernel<D, TO, true, true>), grid, dim3(512), 0, s, p);
-      else hipLaunchKernelGGL((bwd_dkdv_kernel<D, TO, false, true>), grid, dim3(512), 0, s, p);
+      launch_dkdv<D, TO, true>(a, p, grid, s);
     }
     if ((e = hipGetLastError()) != hipSuccess) return e;
     if ((e = launch_kv_combine<D, TO>(a, p, s)) != hipSuccess) return e;
@@ -1017,8 +1032,7 @@ hipError_t launch_bwd_t(const AttnBwdLaunch& a, hipStream_t s) {
   {
     TimingScope t("pp_attn_bwd_dkdv", s);
     const dim3 grid((unsigned)((int64_t)a.n_kv_items * a.hkv));
-    if (a.rope) hipLaunchKernelGGL((bwd_dkdv_kernel<D, TO, true, false>), grid, dim3(512), 0, s, p);
-    else hipLaunchKernelGGL((bwd_dkdv_kernel<D, TO, false, false>), grid, dim3(512), 0, s, p);
+    launch_dkdv<D, TO, false>(a, p, grid, s);
   }
   if ((e = hipGetLastError()) != hipSuccess) return e;
   return launch_kv_combine<D, TO>(a, p, s);
