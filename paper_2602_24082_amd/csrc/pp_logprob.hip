@@ -109,14 +109,26 @@ struct RowSplit {
     nvec = (vocab - head) / N;
     n_extra = vocab - nvec * N;
   }
+  // whether the row starts or ends off a boundary
+  __device__ __forceinline__ bool odd() const { return n_extra > 0; }
   // index of the head or tail element of thread tid (valid for tid < n_extra)
   __device__ __forceinline__ int extra(int tid) const { return tid < head ? tid : tid + nvec * N; }
 };
 
+// A sum of 2^(x*log2e - ml) with ml = m*log2e rounded is off by the factor of that
+// rounding, 2^(m*log2e - ml): up to 1e-6 for logits of 16.  Taken out of the sums of odd
+// rows, whose values had a difference each, (x - m)*log2e, while they were summed one by one
+// (50257 fp32 values: log-probs off by 5.5e-7 rms either way, 5.7e-7 without this).
+__device__ __forceinline__ float exact_base(float s, float m, float ml, bool odd) {
+  constexpr float kLn2 = 0.6931471805599453f;
+  const float off = odd ? fmaf(m, kLog2e, -ml) * kLn2 : 0.f;
+  return fmaf(s, -off, s);
+}
+
 // Online (max, sum) over the vectors first + tid, first + tid + THREADS, ... below
 // nvec of thread tid, kLpUnroll loads in flight.
 template <typename T, int THREADS>
-__device__ __forceinline__ MaxSum stream_max_sum(const u32x4* __restrict__ xv, int first, int nvec) {
+__device__ __forceinline__ MaxSum stream_max_sum(const u32x4* __restrict__ xv, int first, int nvec, bool odd) {
   const int tid = threadIdx.x;
   constexpr int N = Vec16<T>::N;
   MaxSum acc = {kNegInf, 0.f};
@@ -151,7 +163,7 @@ __device__ __forceinline__ MaxSum stream_max_sum(const u32x4* __restrict__ xv, i
           for (int e = 0; e < N; ++e) s += fast_exp2(fmaf(f[j * N + e], kLog2e, -ml));
         }
       }
-      acc = {m, s};
+      acc = {m, exact_base(s, m, ml, odd)};
     }
   }
   return acc;
@@ -231,7 +243,7 @@ __device__ RowLse row_logsumexp(const T* __restrict__ x, int vocab) {
   const RowSplit<T> rs(x, vocab);
   const float xe = tid < rs.n_extra ? elem<T>(x, rs.extra(tid)) : kNegInf;
   const u32x4* xv = reinterpret_cast<const u32x4*>(x + rs.head);
-  MaxSum acc = stream_max_sum<T, kLpThreads>(xv, 0, rs.nvec);
+  MaxSum acc = stream_max_sum<T, kLpThreads>(xv, 0, rs.nvec, rs.odd());
   if (tid < rs.n_extra) acc = combine(acc, MaxSum{xe, 1.f});
   RowLse r = block_lse<kLpThreads>(acc, [] {});
   if (r.redo()) {
@@ -383,7 +395,7 @@ __global__ __launch_bounds__(THREADS, R <= 8 ? 8 : 4) void logprob_bwd_kernel(Lo
     if (y < 0 || y >= vocab) s_bad = 1;
   }
   MaxSum over = {kNegInf, 0.f};  // of the vectors past the registers
-  if constexpr (OVER) over = stream_max_sum<T, THREADS>(xv, R * THREADS, nvec);
+  if constexpr (OVER) over = stream_max_sum<T, THREADS>(xv, R * THREADS, nvec, n_extra > 0);
   // logsumexp of the row from the registers
   float m = kNegInf;
 #pragma unroll
@@ -410,6 +422,7 @@ __global__ __launch_bounds__(THREADS, R <= 8 ? 8 : 4) void logprob_bwd_kernel(Lo
         for (int e = 0; e < N; ++e) s += fast_exp2(fmaf(f[e], kLog2e, -ml));
       }
     }
+    if constexpr (EDGE) s = exact_base(s, m, ml, n_extra > 0);
   }
   MaxSum acc = {m, s};
   if constexpr (OVER) acc = combine(acc, over);
