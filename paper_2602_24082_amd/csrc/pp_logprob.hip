@@ -21,6 +21,8 @@
 #include <hip/hip_runtime.h>
 #include <math.h>
 
+#include <algorithm>
+
 #include "pp_device.h"
 #include "pp_launch.h"
 
@@ -664,10 +666,28 @@ namespace {
 
 // The shape with the most workgroups per compute unit whose registers hold a row
 // of `nvec` 16-byte vectors.
+//
+// In a dense gradient whose rows mostly predict nothing the zeros set the time, and
+// they are written faster by fewer workgroups at once (few rows' lines in flight).
+// Another shape would add a predicting row's sum in another order than the gathered
+// form, so the same one is held to one workgroup a unit by LDS that it does not use.
+// 16000 rows, a share f of them predicting, us with four (two at 50000) / with one:
+//           20000 bf16   12000 fp32   32000 bf16   50000 bf16 (12000 rows)
+//   f .02    144 / 140    164 / 157    214 / 207    281 / 269
+//      .1    158 / 135    179 / 164    240 / 218    299 / 286
+//      .2    171 / 158    192 / 174    259 / 236    316 / 309
+//      .3    178 / 188    204 / 200    273 / 274    336 / 319
+//      .5    198 / 249    231 / 248    303 / 349    370 / 396
+// Below 1700 vectors (12000 bf16) and on rows off the boundaries four are as good.
 template <typename T, bool EDGE>
 void launch_logprob_bwd_rows(const LogprobBwdLaunch& a, int grid, int nvec, hipStream_t s) {
   constexpr int kMost = EDGE ? 18 : 19;
-  auto launch = [&](auto kernel, int threads) { hipLaunchKernelGGL(kernel, dim3(grid), dim3(threads), 0, s, a); };
+  constexpr unsigned kHalfLds = 96 << 10;  // more than half of a unit's 160 KB
+  const bool few = !EDGE && !a.gathered && nvec >= 1700 && nvec <= 1024 * 8 &&
+                   (int64_t)a.n_rows * 14000 <= (int64_t)std::min(nvec, 4900) * a.sumT;
+  auto launch = [&](auto kernel, int threads) {
+    hipLaunchKernelGGL(kernel, dim3(grid), dim3(threads), few ? kHalfLds : 0u, s, a);
+  };
   if (nvec <= 512 * 8) launch(logprob_bwd_kernel<T, 512, 8, EDGE, false>, 512);
   else if (nvec <= 1024 * 8) launch(logprob_bwd_kernel<T, 1024, 8, EDGE, false>, 1024);
   else if (nvec <= 1024 * kMost) launch(logprob_bwd_kernel<T, 1024, kMost, EDGE, false>, 1024);
