@@ -307,15 +307,6 @@ __global__ __launch_bounds__(512, 1) void bwd_dkdv_kernel(BwdParams<TO> p) {
   // either way: 2.4594e-3 of dK on 24 ragged rows.)
   constexpr bool kAccDelta = D == 64;
   bf16x8 kf[D / 16], vf[D / 16];
-  if constexpr (kHoldKV) {
-    wait_vmem<0>();  // this wave's part of K and V (and of the first step) has landed
-    __syncthreads();
-#pragma unroll
-    for (int c = 0; c < D / 16; ++c) {
-      kf[c] = lds_row8<D>(sm.k, kb * 32 + ln, 2 * c + hf);
-      vf[c] = lds_row8<D>(sm.v, kb * 32 + ln, 2 * c + hf);
-    }
-  }
   bool stored = false;  // this wave's last step ended with its two dS stores
 
   for (int n = n_first; n < n_iter; ++n) {
@@ -339,6 +330,15 @@ __global__ __launch_bounds__(512, 1) void bwd_dkdv_kernel(BwdParams<TO> p) {
     }
     if (n + 1 < n_iter) issue(n + 1);
     if (!wave_live) continue;
+    if constexpr (kHoldKV) {
+      if (n == n_first) {  // behind the first step's barrier (one of their own cost tiles of ten steps 2.5%)
+#pragma unroll
+        for (int c = 0; c < D / 16; ++c) {
+          kf[c] = lds_row8<D>(sm.k, kb * 32 + ln, 2 * c + hf);
+          vf[c] = lds_row8<D>(sm.v, kb * 32 + ln, 2 * c + hf);
+        }
+      }
+    }
     const DkdvStage<D>& sg = sm.st[n & 1];
     const int qb0 = qs + qb * 32;
     if (qb0 >= wq_end || qb0 + 31 < wk0) continue;  // no visible pair in the block
